@@ -174,7 +174,7 @@ ivx_status ivx_create(const ivx_dims* dims, int device, ivx_ctx** out) {
   c->TP = tp_size(c->R);
   c->margin = candidate_margin(c->C);
   c->margin_bf16 = candidate_margin_bf16(c->C);
-  c->nhist = (int)((c->maxF + 8191) / 8192);
+  c->nhist = hist_blocks(c->maxF, c->C);
 
   const size_t C = c->C, D = c->D, R = c->R, F = c->maxF;
   bool ok = true;

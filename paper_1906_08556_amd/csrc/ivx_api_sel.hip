@@ -144,7 +144,6 @@ ivx_status ivx_selector_set(ivx_ctx* ctx, const ivx_selector_dims* sd, const flo
   S->ob3 = S->oW3 + C * H2;
   S->P = S->ob3 + C;
   S->chunk = std::min<int64_t>(maxF, (int64_t)1 << 20);
-  const int64_t nbh = maxF / 8192 + 1;
   bool ok = true;
   auto A = [&](bool r) { ok = ok && r; };
   A(salloc(&S->param, S->P));
@@ -168,7 +167,7 @@ ivx_status ivx_selector_set(ivx_ctx* ctx, const ivx_selector_dims* sd, const flo
   A(salloc(&S->score, maxF * k));
   A(salloc(&S->thr, maxF));
   A(salloc(&S->lscore, maxF * k));
-  A(salloc(&S->hist, nbh * C));
+  A(salloc(&S->hist, (int64_t)ctx->nhist * C));
   A(salloc(&S->coff, C + 1));
   A(salloc(&S->ent, maxF * k));
   A(salloc(&S->xfb, maxF * D));
@@ -234,7 +233,7 @@ ivx_status ivx_pruned_set(ivx_ctx* ctx, int32_t k, float prune, void* stream) {
   A(salloc(&P->score, maxF * k));
   A(salloc(&P->thr, maxF));
   A(salloc(&P->lscore, maxF * k));
-  A(salloc(&P->hist, (maxF / 8192 + 1) * C));
+  A(salloc(&P->hist, (int64_t)ctx->nhist * C));
   A(salloc(&P->coff, C + 1));
   A(salloc(&P->ent, maxF * k));
   if (!ok) {

@@ -31,6 +31,22 @@ constexpr int kMaxProposals = 32;
 // more than ln k + 16.64 + 2 nats below the frame's best carry less than
 // 2^-24 e^-2 of its mass; the filter itself is off by far less than 2 nats.
 inline float selection_margin(int k) { return logf((float)k) + 18.64f; }
+// Frame blocks of the counting sorts that bucket (frame, component) slots by
+// component: as many blocks as keep the whole chip busy (each block counts its
+// frames in LDS, C counters per block in device memory, at most 4M counters
+// more than one block per 8192 frames needs).  With one block per 8192 frames
+// a batch of 300k frames ran on 37 of 256 CUs, 0.3 ms per pass.
+constexpr int kHistBlocks = 512;
+inline int hist_blocks(int64_t maxF, int C) {
+  const int64_t least = (maxF + 8191) / 8192, cap = (int64_t(4) << 20) / C;
+  const int64_t want = kHistBlocks < cap ? kHistBlocks : cap;
+  return (int)(least > want ? least : want > 0 ? want : 1);
+}
+// Frames per block of a sort over F frames with room for nhist blocks.
+inline int hist_frames(int64_t F, int nhist) {
+  const int64_t f = (F + nhist - 1) / nhist;
+  return (int)(((f > 256 ? f : 256) + 15) / 16 * 16);
+}
 // Tile size of the tile-packed symmetric layout.
 constexpr int TB = 16;
 
@@ -89,7 +105,7 @@ struct Selector {
   float* score = nullptr;   // [maxF][k] FP32 filter scores
   float* thr = nullptr;     // [maxF] the frame's best filter score minus the margin
   double* lscore = nullptr; // [maxF][k] exact FP64 scores of the kept proposals
-  int* hist = nullptr;      // [maxF / 8192 + 1][C]
+  int* hist = nullptr;      // [ctx->nhist][C]
   int* coff = nullptr;      // [C + 1]
   int2* ent = nullptr;      // [maxF * k] (frame * k + slot, component), by component
   float* xfb = nullptr;     // [maxF][D] fallback frames, gathered
@@ -120,7 +136,7 @@ struct Presel {
   float* score = nullptr;   // [maxF][k]
   float* thr = nullptr;     // [maxF] the frame's best filter score minus the margin
   double* lscore = nullptr; // [maxF][k] exact FP64 scores of the kept proposals
-  int* hist = nullptr;      // [maxF / 8192 + 1][C]
+  int* hist = nullptr;      // [ctx->nhist][C]
   int* coff = nullptr;      // [C + 1]
   int2* ent = nullptr;      // [maxF * k]
 };
@@ -191,7 +207,7 @@ struct ivx_ctx {
   int* coff = nullptr;        // [C+1]
   int2* ent = nullptr;        // [maxF*KP] component-sorted (frame, gamma bits)
   double* partial = nullptr;  // [1024] reduction partials
-  int nhist = 0;
+  int nhist = 0;              // blocks of the counting sorts (hist_blocks)
 
   // TV-derived quantities (recomputed when the TV model changes)
   bool tv_dirty = true;
@@ -313,6 +329,9 @@ void launch_sum_f64(ivx_ctx* ctx, const double* x, int64_t n, double* acc, hipSt
 // ent[0, coff[C]) sorted by component (slot = g * kpf + index, c = .y)
 void launch_exact_sorted(ivx_ctx* ctx, const int2* ent, const int* coff, int kpf, const float* X,
                          double* lscore, hipStream_t s);
+// hist [nb][C] (counts) -> exclusive prefix over the blocks of each component;
+// coff[c] = first entry of component c, coff[C] = total.  Block b's entries of
+// component c start at coff[c] + hist[b][c].
 void launch_hist_scan(int nb, int C, int* hist, int* coff, hipStream_t s);
 
 // ---- ivx_api_tv.hip

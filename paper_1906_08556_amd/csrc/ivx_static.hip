@@ -10,6 +10,7 @@
 // shares that device's array: calls that overlap on one device (two streams,
 // two host threads) race, and each call overwrites everything it reads, so
 // nothing has to be cleared between calls.
+#include <algorithm>
 #include <mutex>
 
 #include "ivx_internal.h"
@@ -27,11 +28,11 @@ void* g_scratch[kMaxDevices] = {};
 
 size_t align256(size_t n) { return (n + 255) / 256 * 256; }
 
-// Bytes of the workspace for F frames and C components, with each piece
-// 256-byte aligned; *off receives the offsets of the seven pieces.
-size_t static_layout(int64_t F, int C, size_t off[7]) {
+// Bytes of the workspace for F frames and C components with nhist blocks of
+// the counting sort, each piece 256-byte aligned; *off receives the offsets of
+// the seven pieces.
+size_t static_layout(int64_t F, int C, size_t nhist, size_t off[7]) {
   const size_t f = (size_t)F, kp = ivx::KP;
-  const size_t nhist = (size_t)((F + 8191) / 8192);
   const size_t sz[7] = {f * kp * sizeof(int2),   // cand
                         f * sizeof(float),       // cM
                         f * sizeof(int),         // cflag
@@ -92,7 +93,17 @@ ivx_status ubm_posteriors_static(ivx_ctx* ctx, const float* X, int64_t F, ivx_pr
     return IVX_EINVAL;
   }
   size_t off[7];
-  const size_t need = static_layout(F, ctx->C, off);
+  // at least one histogram block per 8192 frames; as many as the array has
+  // room for beside the rest, up to what the sort can use
+  const int64_t least = (F + 8191) / 8192;
+  size_t need = static_layout(F, ctx->C, (size_t)least, off);
+  int64_t nhist = least;
+  if (need <= kStaticBytes) {
+    const int64_t room = (int64_t)((kStaticBytes - need) / (sizeof(int) * (size_t)ctx->C + 1));
+    nhist = std::min<int64_t>(ivx::hist_blocks(F, ctx->C), least + room);
+    need = static_layout(F, ctx->C, (size_t)nhist, off);
+    if (need > kStaticBytes) need = static_layout(F, ctx->C, (size_t)(nhist = least), off);
+  }
   if (need > kStaticBytes) {
     ivx::set_error("ubm_posteriors_static: F=%lld frames at C=%d need %zu bytes, more than the "
                    "%zu-byte static workspace (about 392 + C/2048 bytes per frame)",
@@ -124,6 +135,7 @@ ivx_status ubm_posteriors_static(ivx_ctx* ctx, const float* X, int64_t F, ivx_pr
   w.ent = reinterpret_cast<int2*>(b + off[4]);
   w.hist = reinterpret_cast<int*>(b + off[5]);
   w.coff = reinterpret_cast<int*>(b + off[6]);
+  w.nhist = (int)nhist;
   w.prof_on = false;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   ivx::launch_posteriors(&w, X, F, prec, IVX_SEL_ALL, post_idx, post_val, frame_ll, s);

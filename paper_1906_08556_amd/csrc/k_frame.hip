@@ -450,8 +450,6 @@ k_frame_tile_bf16(const float* __restrict__ X, int64_t F, int D, const float* __
 // (per-block histograms, the shared scan, a scatter); k_exact_sorted then
 // walks the sorted slots so that a wave loads each L_c^-1 row once per run
 // of slots of one component instead of once per slot.
-constexpr int RHB = 8192;  // frames per histogram block
-
 __device__ inline int resc_kept(int64_t e, int C, const int2* __restrict__ cand,
                                 const float* __restrict__ cM, float margin,
                                 const int* __restrict__ cflag) {
@@ -462,15 +460,15 @@ __device__ inline int resc_kept(int64_t e, int C, const int2* __restrict__ cand,
 }
 
 __global__ void __launch_bounds__(256)
-k_resc_hist(int64_t F, int C, const int2* __restrict__ cand, const float* __restrict__ cM,
+k_resc_hist(int64_t F, int fpb, int C, const int2* __restrict__ cand, const float* __restrict__ cM,
             float margin, const int* __restrict__ cflag, const int* __restrict__ Fdev,
             int* __restrict__ hist) {
   extern __shared__ int hl[];
   if (Fdev && (int64_t)Fdev[0] < F) F = Fdev[0];
   for (int c = threadIdx.x; c < C; c += 256) hl[c] = 0;
   __syncthreads();
-  const int64_t e0 = (int64_t)blockIdx.x * RHB * KP;
-  const int64_t e1 = min(F * KP, e0 + (int64_t)RHB * KP);
+  const int64_t e0 = (int64_t)blockIdx.x * fpb * KP;
+  const int64_t e1 = min(F * KP, e0 + (int64_t)fpb * KP);
   for (int64_t e = e0 + threadIdx.x; e < e1; e += 256) {
     const int c = resc_kept(e, C, cand, cM, margin, cflag);
     if (c >= 0) atomicAdd(&hl[c], 1);
@@ -480,15 +478,15 @@ k_resc_hist(int64_t F, int C, const int2* __restrict__ cand, const float* __rest
 }
 
 __global__ void __launch_bounds__(256)
-k_resc_scatter(int64_t F, int C, const int2* __restrict__ cand, const float* __restrict__ cM,
+k_resc_scatter(int64_t F, int fpb, int C, const int2* __restrict__ cand, const float* __restrict__ cM,
                float margin, const int* __restrict__ cflag, const int* __restrict__ Fdev,
-               const int* __restrict__ base, int2* __restrict__ ent) {
+               const int* __restrict__ base, const int* __restrict__ coff, int2* __restrict__ ent) {
   extern __shared__ int cur[];
   if (Fdev && (int64_t)Fdev[0] < F) F = Fdev[0];
-  for (int c = threadIdx.x; c < C; c += 256) cur[c] = base[(size_t)blockIdx.x * C + c];
+  for (int c = threadIdx.x; c < C; c += 256) cur[c] = coff[c] + base[(size_t)blockIdx.x * C + c];
   __syncthreads();
-  const int64_t e0 = (int64_t)blockIdx.x * RHB * KP;
-  const int64_t e1 = min(F * KP, e0 + (int64_t)RHB * KP);
+  const int64_t e0 = (int64_t)blockIdx.x * fpb * KP;
+  const int64_t e1 = min(F * KP, e0 + (int64_t)fpb * KP);
   for (int64_t e = e0 + threadIdx.x; e < e1; e += 256) {
     const int c = resc_kept(e, C, cand, cM, margin, cflag);
     if (c >= 0) ent[atomicAdd(&cur[c], 1)] = make_int2((int)e, c);
@@ -755,13 +753,14 @@ void launch_rescore(ivx_ctx* ctx, const float* X, int64_t F, int prec, int* post
   if (F <= 0) return;
   const float margin = prec == IVX_BF16 ? ctx->margin_bf16 : ctx->margin;
   // exact scores of the kept candidates, by component
-  const unsigned nb = (unsigned)((F + RHB - 1) / RHB);
+  const int fpb = hist_frames(F, ctx->nhist);
+  const unsigned nb = (unsigned)((F + fpb - 1) / fpb);
   const size_t ldsc = sizeof(int) * ctx->C;
-  k_resc_hist<<<nb, 256, ldsc, s>>>(F, ctx->C, ctx->cand, ctx->cM, margin, ctx->cflag, Fdev,
+  k_resc_hist<<<nb, 256, ldsc, s>>>(F, fpb, ctx->C, ctx->cand, ctx->cM, margin, ctx->cflag, Fdev,
                                     ctx->hist);
   launch_hist_scan((int)nb, ctx->C, ctx->hist, ctx->coff, s);
-  k_resc_scatter<<<nb, 256, ldsc, s>>>(F, ctx->C, ctx->cand, ctx->cM, margin, ctx->cflag, Fdev,
-                                       ctx->hist, ctx->ent);
+  k_resc_scatter<<<nb, 256, ldsc, s>>>(F, fpb, ctx->C, ctx->cand, ctx->cM, margin, ctx->cflag,
+                                       Fdev, ctx->hist, ctx->coff, ctx->ent);
   launch_exact_sorted(ctx, ctx->ent, ctx->coff, KP, X, ctx->lscore, s);
   const unsigned nblk = (unsigned)((F + 3) / 4);
   k_rescore<<<nblk, 256, 0, s>>>(X, F, ctx->D, ctx->C, ctx->mu, ctx->linv, ctx->cst, ctx->cand,

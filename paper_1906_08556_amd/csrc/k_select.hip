@@ -40,7 +40,6 @@ constexpr int NT = 128;       // output features (components) per MLP tile
 constexpr int KT = 32;        // K per LDS stage
 constexpr int LDK = KT + 8;   // LDS row stride (bf16)
 constexpr int ZS = NT + 1;    // LDS row stride (floats) of a staged logit chunk
-constexpr int HBS = 8192;     // frames per histogram block
 
 __device__ inline uint4 pack8(const float* v) {
   bf16x8 b;
@@ -573,14 +572,14 @@ k_diag_topk(const float* __restrict__ X, int64_t F, int D, const float* __restri
 
 // hist[b][c]: proposals of component c among the kept frames of block b
 __global__ void __launch_bounds__(256)
-k_sel_hist(int64_t F, int k, int C, const int* __restrict__ prop, const int* __restrict__ fb,
+k_sel_hist(int64_t F, int fpb, int k, int C, const int* __restrict__ prop, const int* __restrict__ fb,
            int* __restrict__ hist) {
   extern __shared__ int hl[];
   const int b = blockIdx.x;
   for (int c = threadIdx.x; c < C; c += 256) hl[c] = 0;
   __syncthreads();
-  const int64_t e0 = (int64_t)b * HBS * k;
-  const int64_t e1 = min(F * k, e0 + (int64_t)HBS * k);
+  const int64_t e0 = (int64_t)b * fpb * k;
+  const int64_t e1 = min(F * k, e0 + (int64_t)fpb * k);
   for (int64_t e = e0 + threadIdx.x; e < e1; e += 256) {
     if (fb && fb[e / k]) continue;
     const int c = prop[e];
@@ -591,14 +590,15 @@ k_sel_hist(int64_t F, int k, int C, const int* __restrict__ prop, const int* __r
 }
 
 __global__ void __launch_bounds__(256)
-k_sel_scatter(int64_t F, int k, int C, const int* __restrict__ prop, const int* __restrict__ fb,
-              const int* __restrict__ base, int2* __restrict__ ent) {
+k_sel_scatter(int64_t F, int fpb, int k, int C, const int* __restrict__ prop, const int* __restrict__ fb,
+              const int* __restrict__ base, const int* __restrict__ coff,
+              int2* __restrict__ ent) {
   extern __shared__ int cur[];
   const int b = blockIdx.x;
-  for (int c = threadIdx.x; c < C; c += 256) cur[c] = base[(size_t)b * C + c];
+  for (int c = threadIdx.x; c < C; c += 256) cur[c] = coff[c] + base[(size_t)b * C + c];
   __syncthreads();
-  const int64_t e0 = (int64_t)b * HBS * k;
-  const int64_t e1 = min(F * k, e0 + (int64_t)HBS * k);
+  const int64_t e0 = (int64_t)b * fpb * k;
+  const int64_t e1 = min(F * k, e0 + (int64_t)fpb * k);
   for (int64_t e = e0 + threadIdx.x; e < e1; e += 256) {
     if (fb && fb[e / k]) continue;
     const int c = prop[e];
@@ -633,15 +633,15 @@ __device__ inline int sel_kept(int64_t e, int k, int C, const int* __restrict__ 
 // bucket the kept (frame, proposal) slots by component (as k_sel_hist /
 // k_sel_scatter, restricted to the slots within the margin)
 __global__ void __launch_bounds__(256)
-k_kept_hist(int64_t F, int k, int C, const int* __restrict__ prop, const int* __restrict__ fb,
+k_kept_hist(int64_t F, int fpb, int k, int C, const int* __restrict__ prop, const int* __restrict__ fb,
             const float* __restrict__ score, const float* __restrict__ thr,
             int* __restrict__ hist) {
   extern __shared__ int hl[];
   const int b = blockIdx.x;
   for (int c = threadIdx.x; c < C; c += 256) hl[c] = 0;
   __syncthreads();
-  const int64_t e0 = (int64_t)b * HBS * k;
-  const int64_t e1 = min(F * k, e0 + (int64_t)HBS * k);
+  const int64_t e0 = (int64_t)b * fpb * k;
+  const int64_t e1 = min(F * k, e0 + (int64_t)fpb * k);
   for (int64_t e = e0 + threadIdx.x; e < e1; e += 256) {
     const int c = sel_kept(e, k, C, prop, fb, score, thr);
     if (c >= 0) atomicAdd(&hl[c], 1);
@@ -651,15 +651,16 @@ k_kept_hist(int64_t F, int k, int C, const int* __restrict__ prop, const int* __
 }
 
 __global__ void __launch_bounds__(256)
-k_kept_scatter(int64_t F, int k, int C, const int* __restrict__ prop, const int* __restrict__ fb,
+k_kept_scatter(int64_t F, int fpb, int k, int C, const int* __restrict__ prop, const int* __restrict__ fb,
                const float* __restrict__ score, const float* __restrict__ thr,
-               const int* __restrict__ base, int2* __restrict__ ent) {
+               const int* __restrict__ base, const int* __restrict__ coff,
+              int2* __restrict__ ent) {
   extern __shared__ int cur[];
   const int b = blockIdx.x;
-  for (int c = threadIdx.x; c < C; c += 256) cur[c] = base[(size_t)b * C + c];
+  for (int c = threadIdx.x; c < C; c += 256) cur[c] = coff[c] + base[(size_t)b * C + c];
   __syncthreads();
-  const int64_t e0 = (int64_t)b * HBS * k;
-  const int64_t e1 = min(F * k, e0 + (int64_t)HBS * k);
+  const int64_t e0 = (int64_t)b * fpb * k;
+  const int64_t e1 = min(F * k, e0 + (int64_t)fpb * k);
   for (int64_t e = e0 + threadIdx.x; e < e1; e += 256) {
     const int c = sel_kept(e, k, C, prop, fb, score, thr);
     if (c >= 0) ent[atomicAdd(&cur[c], 1)] = make_int2((int)e, c);
@@ -1125,11 +1126,12 @@ static void exact_kept(ivx_ctx* ctx, const float* X, int64_t F, int k, const int
                 const float* score, float margin, float* thr, int* hist, int* coff, int2* ent,
                 double* lscore, hipStream_t s) {
   k_sel_thr<<<(unsigned)((F + 255) / 256), 256, 0, s>>>(F, k, score, margin, thr);
-  const int nb = (int)((F + HBS - 1) / HBS);
+  const int fpb = hist_frames(F, ctx->nhist), nb = (int)((F + fpb - 1) / fpb);
   const size_t ldsc = sizeof(int) * ctx->C;
-  k_kept_hist<<<nb, 256, ldsc, s>>>(F, k, ctx->C, prop, fb, score, thr, hist);
+  k_kept_hist<<<nb, 256, ldsc, s>>>(F, fpb, k, ctx->C, prop, fb, score, thr, hist);
   launch_hist_scan(nb, ctx->C, hist, coff, s);
-  k_kept_scatter<<<nb, 256, ldsc, s>>>(F, k, ctx->C, prop, fb, score, thr, hist, ent);
+  k_kept_scatter<<<nb, 256, ldsc, s>>>(F, fpb, k, ctx->C, prop, fb, score, thr, hist, coff,
+                                        ent);
   launch_exact_sorted(ctx, ent, coff, k, X, lscore, s);
 }
 
@@ -1140,11 +1142,11 @@ void launch_select_learned(ivx_ctx* ctx, const float* X, int64_t F, int prec, in
   (void)launch_selector_mlp(ctx, X, F, nullptr, nullptr, nullptr, s);  // no copies asked for
   {
     ProfScope ps(ctx, PK_SEL_SCORE, s);
-    const int nb = (int)((F + HBS - 1) / HBS);
+    const int fpb = hist_frames(F, ctx->nhist), nb = (int)((F + fpb - 1) / fpb);
     const size_t ldsc = sizeof(int) * ctx->C;
-    k_sel_hist<<<nb, 256, ldsc, s>>>(F, S.k, ctx->C, S.prop, S.fb, S.hist);
+    k_sel_hist<<<nb, 256, ldsc, s>>>(F, fpb, S.k, ctx->C, S.prop, S.fb, S.hist);
     launch_hist_scan(nb, ctx->C, S.hist, S.coff, s);
-    k_sel_scatter<<<nb, 256, ldsc, s>>>(F, S.k, ctx->C, S.prop, S.fb, S.hist, S.ent);
+    k_sel_scatter<<<nb, 256, ldsc, s>>>(F, fpb, S.k, ctx->C, S.prop, S.fb, S.hist, S.coff, S.ent);
     const int64_t cap = F * S.k;
     k_sel_score<<<(unsigned)((cap + 255) / 256), 256, 0, s>>>(
         X, ctx->D, S.k, S.coff, ctx->C, S.ent, cap, ctx->mu, ctx->linv32r, ctx->cst, S.score);
@@ -1186,11 +1188,11 @@ void launch_select_pruned(ivx_ctx* ctx, const float* X, int64_t F, int* post_idx
 #undef IVX_DIAG
   }
   ProfScope ps(ctx, PK_SEL_SCORE, s);
-  const int nb = (int)((F + HBS - 1) / HBS);
+  const int fpb = hist_frames(F, ctx->nhist), nb = (int)((F + fpb - 1) / fpb);
   const size_t ldsc = sizeof(int) * ctx->C;
-  k_sel_hist<<<nb, 256, ldsc, s>>>(F, P.k, ctx->C, P.prop, nullptr, P.hist);
+  k_sel_hist<<<nb, 256, ldsc, s>>>(F, fpb, P.k, ctx->C, P.prop, nullptr, P.hist);
   launch_hist_scan(nb, ctx->C, P.hist, P.coff, s);
-  k_sel_scatter<<<nb, 256, ldsc, s>>>(F, P.k, ctx->C, P.prop, nullptr, P.hist, P.ent);
+  k_sel_scatter<<<nb, 256, ldsc, s>>>(F, fpb, P.k, ctx->C, P.prop, nullptr, P.hist, P.coff, P.ent);
   const int64_t cap = F * P.k;
   k_sel_score<<<(unsigned)((cap + 255) / 256), 256, 0, s>>>(
       X, ctx->D, P.k, P.coff, ctx->C, P.ent, cap, ctx->mu, ctx->linv32r, ctx->cst, P.score);
