@@ -493,53 +493,61 @@ k_resc_scatter(int64_t F, int fpb, int C, const int2* __restrict__ cand, const f
   }
 }
 
-constexpr int EXC = 64;  // sorted slots per wave chunk
-
 // lscore[slot] = cst_c - 1/2 ||L_c^-1 (x_g - mu_c)||^2 (FP64) for the sorted
 // slots ent[0, coff[C]) (slot = frame * kpf + index), with L_c^-1 read from
 // its dense column-major copy
 // ldense [C][64][64] (zero outside the lower triangle of the D x D block).
 // Lane i holds row i of L_c^-1 and mu_c[i] for the
 // current component; (x - mu)_j reaches all lanes as a broadcast LDS read.
-// Waves take chunks of EXC slots in a grid-stride loop.
+// Waves take chunks of sorted slots in a grid-stride loop.  A slot is a chain
+// of dependent reads (slot, frame, then the sum), so the chunk's slots are
+// read at once into the lanes, the next frame is requested while the current
+// one is scored, the sum runs in four chains, and the chunk shrinks from 64
+// slots down to 2 where there are too few for 8192 waves (one frame block of
+// 130 slots on 3 waves took 155 us).
 __global__ void __launch_bounds__(256)
 k_exact_sorted(const int2* __restrict__ ent, const int* __restrict__ coff, int C, int kpf,
                const float* __restrict__ X, int D, const double* __restrict__ mu,
                const double* __restrict__ ldense, const double* __restrict__ cst,
                double* __restrict__ lscore) {
-  __shared__ double dsh[4][64];
+  __shared__ __attribute__((aligned(16))) double dsh[4][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int64_t total = coff[C];
   const int64_t nw = (int64_t)gridDim.x * 4;
+  const int chunk = (int)max<int64_t>(2, min<int64_t>(64, (total + 8191) / 8192));
   int cur = -1;
   double Lr[64];
   double mul = 0.0, cc = 0.0;
 #pragma unroll
   for (int j = 0; j < 64; ++j) Lr[j] = 0.0;
-  for (int64_t e0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * EXC; e0 < total;
-       e0 += nw * EXC) {
-    const int64_t e1 = min(total, e0 + EXC);
-    for (int64_t e = e0; e < e1; ++e) {
-      const int2 v = ent[e];  // wave-uniform
-      if (v.y != cur) {
-        cur = v.y;
+  for (int64_t e0 = ((int64_t)blockIdx.x * 4 + wv) * chunk; e0 < total; e0 += nw * chunk) {
+    const int ne = (int)min<int64_t>(chunk, total - e0);
+    const int2 mine = lane < ne ? ent[e0 + lane] : make_int2(0, 0);
+    const int frame = mine.x / kpf;
+    float xn = lane < D ? X[(int64_t)__builtin_amdgcn_readlane(frame, 0) * D + lane] : 0.0f;
+    for (int e = 0; e < ne; ++e) {
+      const int c = __builtin_amdgcn_readlane(mine.y, e);
+      const float xv = xn;
+      if (e + 1 < ne && lane < D) xn = X[(int64_t)__builtin_amdgcn_readlane(frame, e + 1) * D + lane];
+      if (c != cur) {
+        cur = c;
         const double* Lc = ldense + (size_t)cur * 4096 + lane;  // column j at Lc[64 j]
 #pragma unroll
         for (int j = 0; j < 64; ++j) Lr[j] = (j < D) ? Lc[64 * j] : 0.0;
         mul = (lane < D) ? mu[(size_t)cur * D + lane] : 0.0;
         cc = cst[cur];
       }
-      const int64_t g = v.x / kpf;
       __builtin_amdgcn_wave_barrier();  // previous slot's reads of dsh are done
-      dsh[wv][lane] = (lane < D) ? (double)X[g * D + lane] - mul : 0.0;
+      dsh[wv][lane] = (lane < D) ? (double)xv - mul : 0.0;
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      double y = 0.0;
+      double y[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int j = 0; j < 64; ++j) y += Lr[j] * dsh[wv][j];
-      const double q = wave_sum(y * y);
-      if (lane == 0) lscore[v.x] = cc - 0.5 * q;
+      for (int j = 0; j < 64; ++j) y[j & 3] += Lr[j] * dsh[wv][j];
+      const double ys = (y[0] + y[1]) + (y[2] + y[3]);
+      const double q = wave_sum(ys * ys);
+      if (lane == 0) lscore[__builtin_amdgcn_readlane(mine.x, e)] = cc - 0.5 * q;
     }
   }
 }
