@@ -122,7 +122,8 @@ void ivx_destroy(ivx_ctx* ctx) {
   selector_free(ctx);
   presel_free(ctx);
   void* ptrs[] = {ctx->w, ctx->mu, ctx->cov, ctx->shift, ctx->Wexp, ctx->W16, ctx->linv,
-                  ctx->linv32r, ctx->ldense, ctx->cst,
+                  ctx->linv32r, ctx->ldense, ctx->cst, ctx->Wd, ctx->wmu, ctx->bnorm, ctx->bmax,
+                  ctx->Wf, ctx->cb, ctx->lquad,
                   ctx->pairs, ctx->T, ctx->Sigma, ctx->p, ctx->bias, ctx->bias32, ctx->cand, ctx->cM, ctx->cflag, ctx->post_idx,
                   ctx->post_val, ctx->frame_ll, ctx->lscore, ctx->hist, ctx->coff, ctx->ent, ctx->partial,
                   ctx->Y32, ctx->V32, ctx->Utp, ctx->Psig, ctx->sig_logdet, ctx->Lbuf, ctx->Wbuf, ctx->Psi64,
@@ -189,6 +190,15 @@ ivx_status ivx_create(const ivx_dims* dims, int device, ivx_ctx** out) {
   A(dalloc(&c->linv32r, C * c->Dp));
   A(dalloc(&c->ldense, C * 4096));
   A(dalloc(&c->cst, C));
+  if (bound_supported(c->C, c->D)) {
+    A(dalloc(&c->Wd, C * 32 * 64));
+    A(dalloc(&c->wmu, C * 32));
+    A(dalloc(&c->bnorm, C));
+    A(dalloc(&c->bmax, 1));
+    A(dalloc(&c->Wf, (size_t)c->Cpad / 2 * 512 * 8));
+    A(dalloc(&c->cb, c->Cpad));
+    A(dalloc(&c->lquad, C * 4096));
+  }
   A(dalloc(&c->pairs, (size_t)c->Kpad));
   A(dalloc(&c->T, C * D * R));
   A(dalloc(&c->Sigma, C * D * D));
@@ -261,7 +271,7 @@ ivx_status ivx_create(const ivx_dims* dims, int device, ivx_ctx** out) {
     set_error("ivx_create: upload failed");
     return IVX_EDEVICE;
   }
-  if (!frame_set_attributes(c) || !select_set_attributes() || !mstep_set_attributes() ||
+  if (!frame_set_attributes(c) || !bound_set_attributes(c) || !select_set_attributes() || !mstep_set_attributes() ||
       !estep_rr_setup()) {
     ivx_destroy(c);
     set_error("ivx_create: hipFuncSetAttribute failed for a large-LDS kernel");
@@ -322,7 +332,7 @@ ivx_status ivx_set_ubm(ivx_ctx* ctx, const double* w, const double* mu, const do
   IVX_HIP(hipMemcpyAsync(ctx->mu, mu, sizeof(double) * ctx->C * ctx->D, hipMemcpyDeviceToDevice, s));
   IVX_HIP(hipMemcpyAsync(ctx->cov, cov, sizeof(double) * ctx->C * ctx->D * ctx->D,
                          hipMemcpyDeviceToDevice, s));
-  launch_ubm_prepare(ctx, s);
+  launch_ubm_prepare(ctx, true, s);
   ivx_status st = after_launch("ivx_set_ubm");
   if (st != IVX_OK) return st;
   st = ivx_sync_status(ctx, stream);

@@ -183,6 +183,15 @@ struct ivx_ctx {
   double* linv = nullptr;     // [C][Dp] L_c^{-1}, lower triangle column by column
   float* linv32r = nullptr;   // [C][Dp] L_c^{-1} in FP32, lower triangle row by row
   double* ldense = nullptr;   // [C][64][64] L_c^{-1} dense, column-major, zero-padded
+  // bound that preselects components in large batches (k_bound.hip; null where
+  // the dimensions do not allow it)
+  float* Wd = nullptr;        // [C][32][64] bound rows W_c (covariances only)
+  float* wmu = nullptr;       // [C][32] W_c (mu_c - shift)
+  float2* bnorm = nullptr;    // [C] Frobenius norms of W_c and W_c (mu_c - shift)
+  int* bmax = nullptr;        // [1] largest magnitude of both (float bits)
+  _Float16* Wf = nullptr;     // [Cpad/2][2][4][64][8] scaled W_c in MFMA fragment order
+  float2* cb = nullptr;       // [Cpad] scaled constants of the bound's test
+  float* lquad = nullptr;     // [C][16][64][4] L_c^{-1} in FP32, four columns per row
   double* cst = nullptr;      // [C] log w_c - D/2 log 2pi - sum_i log L_c[i,i]
   uint16_t* pairs = nullptr;  // [Kpad] expanded-feature index pairs (a | b << 8)
 
@@ -280,7 +289,8 @@ struct ProfScope {
 namespace ivx {
 
 // ---- k_ubm.hip
-void launch_ubm_prepare(ivx_ctx* ctx, hipStream_t s);
+// cov_changed: false when only the means moved (realignment)
+void launch_ubm_prepare(ivx_ctx* ctx, bool cov_changed, hipStream_t s);
 void launch_init_tv(ivx_ctx* ctx, const double* T_rand, double p0, hipStream_t s);
 void launch_init_tv_standard(ivx_ctx* ctx, const double* T_rand, hipStream_t s);
 void launch_bias32(ivx_ctx* ctx, hipStream_t s);
@@ -305,12 +315,25 @@ bool estep_rr_setup();
 // grid is sized for F).  fmap (optional): output row of compact frame i.
 void launch_frame_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
                          const int* Fdev = nullptr);
+// the dense kernel alone, in the launch shape of ctx->tune; flist (optional):
+// frame numbers of the Fdev[0] frames to do
+void launch_frame_dense(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
+                        const int* Fdev = nullptr, const int* flist = nullptr);
 // nf (optional): n/f of every frame's kept posteriors are added to nf->acc.
 void launch_rescore(ivx_ctx* ctx, const float* X, int64_t F, int prec, int* post_idx,
                     float* post_val, double* frame_ll, hipStream_t s, const int* Fdev = nullptr,
                     const int* fmap = nullptr, const NfTarget* nf = nullptr);
 void launch_dense_gamma(ivx_ctx* ctx, int64_t F, const int* post_idx, const float* post_val,
                         float* gamma, hipStream_t s);
+
+// ---- k_bound.hip
+bool bound_supported(int C, int D);
+bool bound_set_attributes(const ivx_ctx* ctx);
+void launch_bound_prepare(ivx_ctx* ctx, bool cov_changed, hipStream_t s);
+// Candidate lists as the dense kernel leaves them; the frames that only the
+// dense kernel can do are listed in *fb_list, their number in *fb_count (device).
+void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
+                         const int* Fdev, int** fb_count, int** fb_list);
 
 // ---- k_stats.hip
 // Frame -> utterance map of the batch in ctx->umap (offsets checked; bad

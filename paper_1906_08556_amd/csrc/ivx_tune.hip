@@ -1,6 +1,7 @@
 // Autotuner: times the candidate launch shapes of the hot-path kernels on the
 // caller's workload with HIP events and keeps the fastest in the context.
-//   frame GEMM (FP32 and BF16 forms): 256 components per launch, or 128
+//   frame GEMM (FP32 and BF16 forms): the default (256 components per launch, with
+//   the bound of k_bound.hip where it applies), or the dense kernel with 128
 //   with one or two 32-frame blocks per wave
 //   n/f statistics: 128 or 256 components per workgroup
 //   linear-term GEMM b = p + F V: number of K splits

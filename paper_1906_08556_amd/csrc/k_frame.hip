@@ -64,10 +64,10 @@ struct FrameState {
 };
 
 __device__ inline void frame_state_init(FrameState& st, int64_t g, int64_t F, int h,
-                                        int2* __restrict__ cand) {
-  st.g = g;
+                                        int2* __restrict__ cand, const int* __restrict__ flist) {
   st.valid = g < F;
-  st.lst = cand + (st.valid ? g : 0) * KP + h * CAPL;
+  st.g = (flist && st.valid) ? flist[g] : g;
+  st.lst = cand + (st.valid ? st.g : 0) * KP + h * CAPL;
   st.M = -INFINITY;
   st.cnt = 0;
   st.ov = false;
@@ -125,13 +125,15 @@ __device__ inline void frame_epilogue(const floatx16 (&acc)[NCB], FrameState& st
 }
 
 // Loads the workgroup's frames as x~ = [1, x - shift] rows of DS floats.
+// flist (optional): the frames' numbers.
 __device__ inline void load_frames(float* xs, int nfr, int DS, const float* __restrict__ X,
-                                   int64_t f0, int64_t F, int D, const float* __restrict__ shift) {
+                                   int64_t f0, int64_t F, int D, const float* __restrict__ shift,
+                                   const int* __restrict__ flist) {
   for (int i = threadIdx.x; i < nfr * DS; i += 256) {
     const int fr = i / DS, a = i - fr * DS;
     const int64_t g = f0 + fr;
     float v = (a == 0) ? 1.0f : 0.0f;
-    if (a > 0 && g < F) v = X[g * D + (a - 1)] - shift[a - 1];
+    if (a > 0 && g < F) v = X[(flist ? flist[g] : g) * D + (a - 1)] - shift[a - 1];
     xs[i] = v;
   }
 }
@@ -153,7 +155,8 @@ __global__ void __launch_bounds__(256, FB == 1 ? 2 : 1)
 k_frame_tile(const float* __restrict__ X, int64_t F, int D, const float* __restrict__ shift,
              const float* __restrict__ W, int C, int Cpad, int Kpad,
              const uint16_t* __restrict__ pairs, float margin, int2* __restrict__ cand,
-             float* __restrict__ cM, int* __restrict__ cflag, const int* __restrict__ Fdev) {
+             float* __restrict__ cM, int* __restrict__ cflag, const int* __restrict__ Fdev,
+             const int* __restrict__ flist) {
   constexpr int CT = 32 * NCB;   // components per component tile
   constexpr int TPC = 256 / CT;  // threads per staged component
   constexpr int NV = 2 / TPC;    // float4 per thread and chunk
@@ -192,11 +195,11 @@ k_frame_tile(const float* __restrict__ X, int64_t F, int D, const float* __restr
   for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
     const int64_t f0 = tile * FTB;
     __syncthreads();  // the previous tile's readers of xs and Ws are done
-    load_frames(xs, FTB, DS, X, f0, F, D, shift);
+    load_frames(xs, FTB, DS, X, f0, F, D, shift, flist);
     FrameState st[FB];
 #pragma unroll
     for (int fb = 0; fb < FB; ++fb)
-      frame_state_init(st[fb], f0 + (wave * FB + fb) * FR + l32, F, h, cand);
+      frame_state_init(st[fb], f0 + (wave * FB + fb) * FR + l32, F, h, cand, flist);
     for (int c0 = 0; c0 < Cpad; c0 += CT) {
       gload(0, c0);
       sstore(0);
@@ -253,7 +256,8 @@ k_frame_tile_direct(const float* __restrict__ X, int64_t F, int D,
                     const float* __restrict__ shift, const float* __restrict__ W, int C, int Cpad,
                     int Kpad, const uint16_t* __restrict__ pairs, float margin,
                     int2* __restrict__ cand, float* __restrict__ cM, int* __restrict__ cflag,
-                    const int* __restrict__ Fdev) {
+                    const int* __restrict__ Fdev,
+             const int* __restrict__ flist) {
   constexpr int CT = 32 * NCB;  // components per component tile
   extern __shared__ float smem[];
   if (Fdev && (int64_t)Fdev[0] < F) F = Fdev[0];
@@ -272,9 +276,9 @@ k_frame_tile_direct(const float* __restrict__ X, int64_t F, int D,
   for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
     const int64_t f0 = tile * FT;
     __syncthreads();  // the previous tile's readers of xs are done
-    load_frames(xs, FT, DS, X, f0, F, D, shift);
+    load_frames(xs, FT, DS, X, f0, F, D, shift, flist);
     FrameState st;
-    frame_state_init(st, f0 + wave * FR + l32, F, h, cand);
+    frame_state_init(st, f0 + wave * FR + l32, F, h, cand, flist);
     __syncthreads();
     for (int c0 = 0; c0 < Cpad; c0 += CT) {
       // lane's coefficients: chunk q, component c0 + 32 cb + l32, features 4h..4h+3
@@ -335,7 +339,8 @@ __global__ void __launch_bounds__(256, FB == 1 ? 2 : 1)
 k_frame_tile_bf16(const float* __restrict__ X, int64_t F, int D, const float* __restrict__ shift,
                   const __bf16* __restrict__ W16, int C, int Cpad, int Kpad,
                   const uint16_t* __restrict__ pairs, float margin, int2* __restrict__ cand,
-                  float* __restrict__ cM, int* __restrict__ cflag, const int* __restrict__ Fdev) {
+                  float* __restrict__ cM, int* __restrict__ cflag, const int* __restrict__ Fdev,
+             const int* __restrict__ flist) {
   constexpr int CT = 32 * NCB;   // components per component tile
   constexpr int TPC = 256 / CT;  // threads per staged component
   constexpr int NV = 4 / TPC;    // uint4 (8 bf16) per thread and chunk
@@ -380,11 +385,11 @@ k_frame_tile_bf16(const float* __restrict__ X, int64_t F, int D, const float* __
   for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
     const int64_t f0 = tile * FTB;
     __syncthreads();  // the previous tile's readers of xs and Ws are done
-    load_frames(xs, FTB, DS, X, f0, F, D, shift);
+    load_frames(xs, FTB, DS, X, f0, F, D, shift, flist);
     FrameState st[FB];
 #pragma unroll
     for (int fb = 0; fb < FB; ++fb)
-      frame_state_init(st[fb], f0 + (wave * FB + fb) * FR + l32, F, h, cand);
+      frame_state_init(st[fb], f0 + (wave * FB + fb) * FR + l32, F, h, cand, flist);
     for (int c0 = 0; c0 < Cpad; c0 += CT) {
       gload(0, c0);
       sstore(0);
@@ -693,7 +698,7 @@ size_t frame_lds_f32(int D, int Kpad) {
 
 template <int NCB, int FB>
 void frame_launches(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
-                    const int* Fdev) {
+                    const int* Fdev, const int* flist) {
   // persistent grid: as many workgroups as fit on the device at once
   const int64_t ntile = (F + FT * FB - 1) / (FT * FB);
   const unsigned nblk =
@@ -703,7 +708,7 @@ void frame_launches(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream
     const size_t lds = frame_lds_bf16<NCB, FB>(ctx->D, ctx->Kpad);
     k_frame_tile_bf16<NCB, FB><<<nblk, 256, lds, s>>>(
         X, F, ctx->D, ctx->shift, ctx->W16, ctx->C, ctx->Cpad, ctx->Kpad, ctx->pairs,
-        ctx->margin_bf16, ctx->cand, ctx->cM, ctx->cflag, Fdev);
+        ctx->margin_bf16, ctx->cand, ctx->cM, ctx->cflag, Fdev, flist);
     return;
   }
   if (FB == 1 && ctx->tune.frame_direct) {
@@ -712,13 +717,13 @@ void frame_launches(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream
         (unsigned)std::min<int64_t>(ntile, (int64_t)ctx->ncu * (NCB == 4 ? 3 : 2));
     k_frame_tile_direct<NCB><<<nd, 256, frame_lds_direct(ctx->D, ctx->Kpad), s>>>(
         X, F, ctx->D, ctx->shift, ctx->Wexp, ctx->C, ctx->Cpad, ctx->Kpad, ctx->pairs,
-        ctx->margin, ctx->cand, ctx->cM, ctx->cflag, Fdev);
+        ctx->margin, ctx->cand, ctx->cM, ctx->cflag, Fdev, flist);
     return;
   }
   const size_t lds = frame_lds_f32<NCB, FB>(ctx->D, ctx->Kpad);
   k_frame_tile<NCB, FB><<<nblk, 256, lds, s>>>(X, F, ctx->D, ctx->shift, ctx->Wexp, ctx->C,
                                                ctx->Cpad, ctx->Kpad, ctx->pairs, ctx->margin,
-                                               ctx->cand, ctx->cM, ctx->cflag, Fdev);
+                                               ctx->cand, ctx->cM, ctx->cflag, Fdev, flist);
 }
 
 }  // namespace
@@ -741,18 +746,35 @@ bool frame_set_attributes(const ivx_ctx* ctx) {
   return ok;
 }
 
-void launch_frame_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
-                         const int* Fdev) {
+void launch_frame_dense(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
+                        const int* Fdev, const int* flist) {
   if (F <= 0) return;
   // frame_ncb: 8 (256 components per launch, one 32-frame block per wave),
   // 4 (128 components), or 2 (128 components, two frame blocks per wave)
   const int ncb = (prec == IVX_BF16) ? ctx->tune.frame_ncb_bf16 : ctx->tune.frame_ncb;
   if (ncb == 4)
-    frame_launches<4, 1>(ctx, X, F, prec, s, Fdev);
+    frame_launches<4, 1>(ctx, X, F, prec, s, Fdev, flist);
   else if (ncb == 2)
-    frame_launches<4, 2>(ctx, X, F, prec, s, Fdev);
+    frame_launches<4, 2>(ctx, X, F, prec, s, Fdev, flist);
   else
-    frame_launches<8, 1>(ctx, X, F, prec, s, Fdev);
+    frame_launches<8, 1>(ctx, X, F, prec, s, Fdev, flist);
+}
+
+// The bound (k_bound.hip) serves the default launch shape wherever it applies;
+// an explicitly chosen shape runs the dense kernel.  Its list positions are
+// 32-bit (64 per frame).
+void launch_frame_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
+                         const int* Fdev) {
+  if (F <= 0) return;
+  const bool chosen = prec == IVX_BF16 ? ctx->tune.frame_ncb_bf16 != 8
+                                       : ctx->tune.frame_ncb != 8 || ctx->tune.frame_direct;
+  if (ctx->Wf && !chosen && F < (int64_t(1) << 25)) {
+    int *fb_count, *fb_list;
+    launch_bound_select(ctx, X, F, prec, s, Fdev, &fb_count, &fb_list);
+    launch_frame_dense(ctx, X, F, prec, s, fb_count, fb_list);
+    return;
+  }
+  launch_frame_dense(ctx, X, F, prec, s, Fdev);
 }
 
 void launch_rescore(ivx_ctx* ctx, const float* X, int64_t F, int prec, int* post_idx,

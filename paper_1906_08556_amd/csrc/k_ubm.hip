@@ -22,8 +22,10 @@ constexpr double kLog2Pi = 1.8378770664093454836;
 
 __global__ void __launch_bounds__(64) k_ubm_shift(const double* __restrict__ w,
                                                   const double* __restrict__ mu, int C, int D,
-                                                  float* __restrict__ shift) {
+                                                  float* __restrict__ shift,
+                                                  int* __restrict__ bmax) {
   const int d = threadIdx.x;
+  if (d == 0 && bmax) bmax[0] = 0;  // taken by k_bound_scale
   if (d >= D) return;
   double s = 0.0, sw = 0.0;
   for (int c = 0; c < C; ++c) {
@@ -224,13 +226,14 @@ __global__ void k_update_means(const double* __restrict__ T, const double* __res
 
 }  // namespace
 
-void launch_ubm_prepare(ivx_ctx* ctx, hipStream_t s) {
-  k_ubm_shift<<<1, 64, 0, s>>>(ctx->w, ctx->mu, ctx->C, ctx->D, ctx->shift);
+void launch_ubm_prepare(ivx_ctx* ctx, bool cov_changed, hipStream_t s) {
+  k_ubm_shift<<<1, 64, 0, s>>>(ctx->w, ctx->mu, ctx->C, ctx->D, ctx->shift, ctx->bmax);
   const size_t lds = 2 * sizeof(double) * ctx->D * ctx->D;
   k_ubm_prepare<<<ctx->Cpad, 64, lds, s>>>(ctx->w, ctx->mu, ctx->cov, ctx->shift, ctx->C, ctx->D,
                                            ctx->K, ctx->Kpad, ctx->pairs, ctx->Wexp, ctx->W16,
                                            ctx->linv, ctx->linv32r, ctx->cst, ctx->dev_err);
   k_linv_dense<<<2048, 256, 0, s>>>(ctx->linv, ctx->C, ctx->D, ctx->ldense);
+  launch_bound_prepare(ctx, cov_changed, s);
 }
 
 void launch_init_tv(ivx_ctx* ctx, const double* T_rand, double p0, hipStream_t s) {
@@ -251,7 +254,7 @@ void launch_bias32(ivx_ctx* ctx, hipStream_t s) {
 void launch_update_means(ivx_ctx* ctx, hipStream_t s) {
   const int n = ctx->C * ctx->D;
   k_update_means<<<(n + 255) / 256, 256, 0, s>>>(ctx->T, ctx->p, ctx->C, ctx->D, ctx->R, ctx->mu);
-  launch_ubm_prepare(ctx, s);
+  launch_ubm_prepare(ctx, false, s);
 }
 
 }  // namespace ivx

@@ -56,3 +56,44 @@ def test_posteriors_and_statistics_at_block_edges(C, F):
     absS = np.einsum("tc,ti,tj->cij", g_ref, np.abs(wl.X), np.abs(wl.X))
     err = np.abs(S.cpu().numpy() - packed_upper(S_ref))
     assert np.all(err <= 2e-7 * packed_upper(absS) + 1e-9 + 1e-6 * np.abs(wl.X).max() ** 2)
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("C,D", [(512, 32), (701, 62), (2048, 60)])
+def test_bound_route_equals_dense_route(C, D, prec):
+    """Large batches preselect components by a bound; the posterior lists are
+    those of the dense kernel, bit for bit, on ordinary frames, on frames with
+    many near-equal components (more than a list holds; far from
+    the other frames, whose lists they would fill at the edge of the margin), and on frames that
+    the bound cannot serve (features beyond FP16 scaling, not finite)."""
+    from paper_1906_08556_amd import ivx
+    F = 20011
+    wl = synth.make(2, C=C, D=D, R=4, U=20, lengths="uniform:1001:1001")
+    X = wl.X[:F].copy()
+    mu, cov = wl.mu.copy(), wl.cov.copy()
+    # the last 100 components nearly the same: frames drawn at their mean meet
+    # lists of more than 32 candidates per half (last, so that the dense kernel
+    # has the other components' scores before it counts candidates)
+    mu[-100:] = mu[-1] + 50.0 + 1e-3 * np.arange(100)[:, None]
+    cov[-100:] = cov[-1]
+    rng = np.random.default_rng(5)
+    X[100:140] = mu[-50] + rng.standard_normal((40, D)) @ np.linalg.cholesky(cov[-1]).T
+    X[200:210] *= 1e4
+    X[300] = 3e7      # beyond 2^23: the dense kernel's
+    X[301, D - 1] = np.inf
+    X[F - 1, 0] = np.nan
+    ctx = ivx.Context(C, D, 4, 1, F)
+    ctx.set_ubm(dev(wl.w), dev(mu), dev(cov))
+    got = []
+    for ncb in (8, 4):  # 8: the bound; an explicitly chosen shape: dense
+        ctx.tuning_set(frame_ncb=ncb, frame_ncb_bf16=ncb)
+        pi = torch.full((F, 16), -7, dtype=torch.int32, device="cuda")
+        pv = torch.full((F, 16), -7.0, device="cuda")
+        ll = torch.full((F,), -7.0, dtype=torch.float64, device="cuda")
+        ctx.ubm_posteriors(dev(X), post_idx=pi, post_val=pv, frame_ll=ll, prec=prec)
+        with pytest.raises(ivx.IvxError):  # the non-finite frames, the flat ones
+            ctx.sync_status()
+        got.append((pi.cpu().numpy(), pv.cpu().numpy(), ll.cpu().numpy()))
+    assert np.all(got[0][0][100:140] >= C - 100)  # 16 of the near-equal ones
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
