@@ -1,4 +1,5 @@
 // C ABI entry points: argument validation, context lifecycle, launch order.
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -124,7 +125,7 @@ void ivx_destroy(ivx_ctx* ctx) {
   void* ptrs[] = {ctx->w, ctx->mu, ctx->cov, ctx->shift, ctx->Wexp, ctx->W16, ctx->linv,
                   ctx->linv32r, ctx->ldense, ctx->cst, ctx->Wd, ctx->wmu, ctx->bnorm, ctx->bmax,
                   ctx->Wf, ctx->cb, ctx->lquad,
-                  ctx->pairs, ctx->T, ctx->Sigma, ctx->p, ctx->bias, ctx->bias32, ctx->cand, ctx->cM, ctx->cflag, ctx->post_idx,
+                  ctx->pairs, ctx->T, ctx->Sigma, ctx->p, ctx->bias, ctx->bias32, ctx->scores, ctx->cand, ctx->cM, ctx->cflag, ctx->post_idx,
                   ctx->post_val, ctx->frame_ll, ctx->lscore, ctx->hist, ctx->coff, ctx->ent, ctx->partial,
                   ctx->Y32, ctx->V32, ctx->Utp, ctx->Psig, ctx->sig_logdet, ctx->Lbuf, ctx->Wbuf, ctx->Psi64,
                   ctx->bpart, ctx->colpart, ctx->bvec, ctx->llu, ctx->n_ws, ctx->f_ws, ctx->Tnew, ctx->obj_part,
@@ -205,6 +206,8 @@ ivx_status ivx_create(const ivx_dims* dims, int device, ivx_ctx** out) {
   A(dalloc(&c->p, R));
   A(dalloc(&c->bias, C * D));
   A(dalloc(&c->bias32, C * D));
+  c->scores_bytes = std::min(kScoresBytes, F * (size_t)c->Cpad * sizeof(float));
+  A(dalloc(&c->scores, c->scores_bytes / sizeof(float)));
   A(dalloc(&c->cand, F * KP));
   A(dalloc(&c->cM, F));
   A(dalloc(&c->cflag, F));

@@ -47,6 +47,8 @@ inline int hist_frames(int64_t F, int nhist) {
   const int64_t f = (F + nhist - 1) / nhist;
   return (int)(((f > 256 ? f : 256) + 15) / 16 * 16);
 }
+// Score buffer of small batches (8192 frames at C = 2048).
+constexpr size_t kScoresBytes = size_t(64) << 20;
 // Tile size of the tile-packed symmetric layout.
 constexpr int TB = 16;
 
@@ -212,6 +214,8 @@ struct ivx_ctx {
   float* post_val = nullptr;  // [maxF][KP]
   double* frame_ll = nullptr; // [maxF]
   double* lscore = nullptr;   // [maxF][KP] exact FP64 scores of the kept candidates
+  float* scores = nullptr;    // [frames][Cpad] scores of a small batch
+  size_t scores_bytes = 0;
   int* hist = nullptr;        // [nhist][C]
   int* coff = nullptr;        // [C+1]
   int2* ent = nullptr;        // [maxF*KP] component-sorted (frame, gamma bits)
@@ -316,15 +320,23 @@ bool estep_rr_setup();
 void launch_frame_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
                          const int* Fdev = nullptr);
 // the dense kernel alone, in the launch shape of ctx->tune; flist (optional):
-// frame numbers of the Fdev[0] frames to do
+// frame numbers of the Fdev[0] frames to do, if those are more than fmin
 void launch_frame_dense(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
-                        const int* Fdev = nullptr, const int* flist = nullptr);
+                        const int* Fdev = nullptr, const int* flist = nullptr, int64_t fmin = 0);
 // nf (optional): n/f of every frame's kept posteriors are added to nf->acc.
 void launch_rescore(ivx_ctx* ctx, const float* X, int64_t F, int prec, int* post_idx,
                     float* post_val, double* frame_ll, hipStream_t s, const int* Fdev = nullptr,
                     const int* fmap = nullptr, const NfTarget* nf = nullptr);
 void launch_dense_gamma(ivx_ctx* ctx, int64_t F, const int* post_idx, const float* post_val,
                         float* gamma, hipStream_t s);
+
+// ---- k_scores.hip
+// Largest batch that fits the score buffer of the context.
+int64_t scores_frames(const ivx_ctx* ctx);
+// Candidate lists of a small batch (at most scores_frames(); a device count
+// Fdev[0] beyond it is left alone, for the dense kernel).
+void launch_scores_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
+                          const int* Fdev, const int* flist);
 
 // ---- k_bound.hip
 bool bound_supported(int C, int D);

@@ -135,6 +135,9 @@ ivx_status ubm_posteriors_static(ivx_ctx* ctx, const float* X, int64_t F, ivx_pr
   w.ent = reinterpret_cast<int2*>(b + off[4]);
   w.hist = reinterpret_cast<int*>(b + off[5]);
   w.coff = reinterpret_cast<int*>(b + off[6]);
+  // what is left of the array holds the scores of a small batch
+  w.scores = reinterpret_cast<float*>(b + need);
+  w.scores_bytes = kStaticBytes - need;
   w.nhist = (int)nhist;
   w.prof_on = false;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);

@@ -156,13 +156,14 @@ k_frame_tile(const float* __restrict__ X, int64_t F, int D, const float* __restr
              const float* __restrict__ W, int C, int Cpad, int Kpad,
              const uint16_t* __restrict__ pairs, float margin, int2* __restrict__ cand,
              float* __restrict__ cM, int* __restrict__ cflag, const int* __restrict__ Fdev,
-             const int* __restrict__ flist) {
+             const int* __restrict__ flist, int64_t fmin) {
   constexpr int CT = 32 * NCB;   // components per component tile
   constexpr int TPC = 256 / CT;  // threads per staged component
   constexpr int NV = 2 / TPC;    // float4 per thread and chunk
   constexpr int FTB = FT * FB;   // frames per workgroup tile
   extern __shared__ float smem[];
   if (Fdev && (int64_t)Fdev[0] < F) F = Fdev[0];
+  if (F <= fmin) return;  // done in another way
   const int64_t ntile = (F + FTB - 1) / FTB;
   if ((int64_t)blockIdx.x >= ntile) return;  // whole workgroup, before any barrier
   const int DS = D + 1;
@@ -257,10 +258,11 @@ k_frame_tile_direct(const float* __restrict__ X, int64_t F, int D,
                     int Kpad, const uint16_t* __restrict__ pairs, float margin,
                     int2* __restrict__ cand, float* __restrict__ cM, int* __restrict__ cflag,
                     const int* __restrict__ Fdev,
-             const int* __restrict__ flist) {
+             const int* __restrict__ flist, int64_t fmin) {
   constexpr int CT = 32 * NCB;  // components per component tile
   extern __shared__ float smem[];
   if (Fdev && (int64_t)Fdev[0] < F) F = Fdev[0];
+  if (F <= fmin) return;  // done in another way
   const int64_t ntile = (F + FT - 1) / FT;
   if ((int64_t)blockIdx.x >= ntile) return;  // whole workgroup, before any barrier
   const int DS = D + 1;
@@ -340,13 +342,14 @@ k_frame_tile_bf16(const float* __restrict__ X, int64_t F, int D, const float* __
                   const __bf16* __restrict__ W16, int C, int Cpad, int Kpad,
                   const uint16_t* __restrict__ pairs, float margin, int2* __restrict__ cand,
                   float* __restrict__ cM, int* __restrict__ cflag, const int* __restrict__ Fdev,
-             const int* __restrict__ flist) {
+             const int* __restrict__ flist, int64_t fmin) {
   constexpr int CT = 32 * NCB;   // components per component tile
   constexpr int TPC = 256 / CT;  // threads per staged component
   constexpr int NV = 4 / TPC;    // uint4 (8 bf16) per thread and chunk
   constexpr int FTB = FT * FB;   // frames per workgroup tile
   extern __shared__ float smem[];
   if (Fdev && (int64_t)Fdev[0] < F) F = Fdev[0];
+  if (F <= fmin) return;  // done in another way
   const int64_t ntile = (F + FTB - 1) / FTB;
   if ((int64_t)blockIdx.x >= ntile) return;  // whole workgroup, before any barrier
   const int DS = D + 1;
@@ -698,7 +701,7 @@ size_t frame_lds_f32(int D, int Kpad) {
 
 template <int NCB, int FB>
 void frame_launches(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
-                    const int* Fdev, const int* flist) {
+                    const int* Fdev, const int* flist, int64_t fmin) {
   // persistent grid: as many workgroups as fit on the device at once
   const int64_t ntile = (F + FT * FB - 1) / (FT * FB);
   const unsigned nblk =
@@ -708,7 +711,7 @@ void frame_launches(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream
     const size_t lds = frame_lds_bf16<NCB, FB>(ctx->D, ctx->Kpad);
     k_frame_tile_bf16<NCB, FB><<<nblk, 256, lds, s>>>(
         X, F, ctx->D, ctx->shift, ctx->W16, ctx->C, ctx->Cpad, ctx->Kpad, ctx->pairs,
-        ctx->margin_bf16, ctx->cand, ctx->cM, ctx->cflag, Fdev, flist);
+        ctx->margin_bf16, ctx->cand, ctx->cM, ctx->cflag, Fdev, flist, fmin);
     return;
   }
   if (FB == 1 && ctx->tune.frame_direct) {
@@ -717,13 +720,13 @@ void frame_launches(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream
         (unsigned)std::min<int64_t>(ntile, (int64_t)ctx->ncu * (NCB == 4 ? 3 : 2));
     k_frame_tile_direct<NCB><<<nd, 256, frame_lds_direct(ctx->D, ctx->Kpad), s>>>(
         X, F, ctx->D, ctx->shift, ctx->Wexp, ctx->C, ctx->Cpad, ctx->Kpad, ctx->pairs,
-        ctx->margin, ctx->cand, ctx->cM, ctx->cflag, Fdev, flist);
+        ctx->margin, ctx->cand, ctx->cM, ctx->cflag, Fdev, flist, fmin);
     return;
   }
   const size_t lds = frame_lds_f32<NCB, FB>(ctx->D, ctx->Kpad);
   k_frame_tile<NCB, FB><<<nblk, 256, lds, s>>>(X, F, ctx->D, ctx->shift, ctx->Wexp, ctx->C,
                                                ctx->Cpad, ctx->Kpad, ctx->pairs, ctx->margin,
-                                               ctx->cand, ctx->cM, ctx->cflag, Fdev, flist);
+                                               ctx->cand, ctx->cM, ctx->cflag, Fdev, flist, fmin);
 }
 
 }  // namespace
@@ -747,31 +750,42 @@ bool frame_set_attributes(const ivx_ctx* ctx) {
 }
 
 void launch_frame_dense(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
-                        const int* Fdev, const int* flist) {
+                        const int* Fdev, const int* flist, int64_t fmin) {
   if (F <= 0) return;
   // frame_ncb: 8 (256 components per launch, one 32-frame block per wave),
   // 4 (128 components), or 2 (128 components, two frame blocks per wave)
   const int ncb = (prec == IVX_BF16) ? ctx->tune.frame_ncb_bf16 : ctx->tune.frame_ncb;
   if (ncb == 4)
-    frame_launches<4, 1>(ctx, X, F, prec, s, Fdev, flist);
+    frame_launches<4, 1>(ctx, X, F, prec, s, Fdev, flist, fmin);
   else if (ncb == 2)
-    frame_launches<4, 2>(ctx, X, F, prec, s, Fdev, flist);
+    frame_launches<4, 2>(ctx, X, F, prec, s, Fdev, flist, fmin);
   else
-    frame_launches<8, 1>(ctx, X, F, prec, s, Fdev, flist);
+    frame_launches<8, 1>(ctx, X, F, prec, s, Fdev, flist, fmin);
 }
 
-// The bound (k_bound.hip) serves the default launch shape wherever it applies;
-// an explicitly chosen shape runs the dense kernel.  Its list positions are
-// 32-bit (64 per frame).
+// Routes of the default launch shape (an explicitly chosen one runs the dense
+// kernel).  All give the same candidate lists.
+//  * at most scores_frames() frames (8192 at C = 2048): scores split over
+//    components (k_scores.hip);
+//  * more, where the bound's conditions hold and its 32-bit list positions (64
+//    per frame) suffice: the bound (k_bound.hip), the frames it cannot serve
+//    as above, or by the dense kernel when they are too many;
+//  * else the dense kernel.
 void launch_frame_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
                          const int* Fdev) {
   if (F <= 0) return;
   const bool chosen = prec == IVX_BF16 ? ctx->tune.frame_ncb_bf16 != 8
                                        : ctx->tune.frame_ncb != 8 || ctx->tune.frame_direct;
-  if (ctx->Wf && !chosen && F < (int64_t(1) << 25)) {
+  const int64_t fs = scores_frames(ctx);
+  if (!chosen && F <= fs) {
+    launch_scores_select(ctx, X, F, prec, s, Fdev, nullptr);
+    return;
+  }
+  if (!chosen && ctx->Wf && F < (int64_t(1) << 25)) {
     int *fb_count, *fb_list;
     launch_bound_select(ctx, X, F, prec, s, Fdev, &fb_count, &fb_list);
-    launch_frame_dense(ctx, X, F, prec, s, fb_count, fb_list);
+    launch_scores_select(ctx, X, F, prec, s, fb_count, fb_list);
+    launch_frame_dense(ctx, X, F, prec, s, fb_count, fb_list, fs);
     return;
   }
   launch_frame_dense(ctx, X, F, prec, s, Fdev);

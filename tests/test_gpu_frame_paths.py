@@ -97,3 +97,20 @@ def test_bound_route_equals_dense_route(C, D, prec):
     assert np.all(got[0][0][100:140] >= C - 100)  # 16 of the near-equal ones
     for a, b in zip(*got):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("C,D,F", [(1, 3, 1), (63, 20, 15), (65, 20, 17), (130, 61, 33),
+                                   (2048, 60, 1), (2048, 60, 100), (700, 63, 1030)])
+def test_small_batch_route_equals_dense_route(C, D, F, prec):
+    """Small batches split the scores over components: the same lists, bit for
+    bit, as the dense kernel with 128 components per launch (component counts
+    up to one launch, or far more, with well separated scores)."""
+    wl = synth.make(2, C=C, D=D, R=4, U=1, lengths=f"uniform:{F}:{F}")
+    ctx = make_ctx(wl)
+    X = dev(wl.X)
+    a = _lists(ctx, X, prec)
+    ctx.tuning_set(frame_ncb=4, frame_ncb_bf16=4)
+    b = _lists(ctx, X, prec)
+    for p, q in zip(a, b):
+        np.testing.assert_array_equal(p, q)
