@@ -18,7 +18,7 @@ void selector_free(ivx_ctx* ctx) {
                   S->W2b, S->W3b, S->b3p, S->h1b, S->h2b, S->prop, S->mass, S->fb, S->fb_list,
                   S->counters, S->score, S->thr, S->lscore, S->hist, S->coff, S->ent, S->xfb,
                   S->xs, S->a1, S->h1,
-                  S->a2, S->h2, S->z, S->dz, S->dh1, S->dh2, S->loss_part, S->colpart};
+                  S->a2, S->h2, S->z, S->dz, S->dh1, S->dh2, S->loss_part, S->colpart, S->gws};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);  // teardown
   delete S;
@@ -183,6 +183,9 @@ ivx_status ivx_selector_set(ivx_ctx* ctx, const ivx_selector_dims* sd, const flo
     A(salloc(&S->dh2, B * H2));
     A(salloc(&S->loss_part, B));
     A(salloc(&S->colpart, 32 * std::max<int64_t>(C, std::max(H1, H2))));
+    // eight splits of the largest weight gradient (dW3 at C = 2048, H2 = 512: 32 MB)
+    S->gws_elems = 8 * std::max<int64_t>(C * H2, H2 * H1);
+    A(salloc(&S->gws, S->gws_elems));
   }
   if (!ok) {
     selector_free(ctx);

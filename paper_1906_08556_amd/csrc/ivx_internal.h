@@ -123,6 +123,8 @@ struct Selector {
   float* dh2 = nullptr;     // [Bmax][H2]
   double* loss_part = nullptr;  // [Bmax]
   float* colpart = nullptr;     // [32][max(C, H1, H2)] column-sum partials
+  float* gws = nullptr;         // [gws_elems] partial products of the split GEMMs
+  int64_t gws_elems = 0;
 };
 
 // State of the pruned alignment (Sec. 4.2): diagonal-UBM coefficients and

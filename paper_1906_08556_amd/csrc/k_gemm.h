@@ -7,12 +7,12 @@
 
 namespace ivx {
 
-enum { GEMM_STORE = 0, GEMM_ADD_F64 = 1, GEMM_STORE_TP = 2 };
+enum { GEMM_STORE = 0, GEMM_STORE_TP = 2 };
 
 struct GemmArgs {
   const float* A = nullptr;
   const float* B = nullptr;
-  void* C = nullptr;
+  float* C = nullptr;
   int64_t lda = 0, ldb = 0, ldc = 0;
   int M = 0, N = 0, K = 0;
   int64_t sA = 0, sB = 0, sC = 0;  // per-batch strides (elements)
@@ -23,9 +23,14 @@ struct GemmArgs {
 };
 
 // C = op(A) op(B).  ta / tb select the transposed addressing of A / B, epi one
-// of GEMM_STORE, GEMM_ADD_F64, GEMM_STORE_TP.  Returns false (and launches
+// of GEMM_STORE, GEMM_STORE_TP.  Returns false (and launches
 // nothing) for a combination that is not instantiated.
 bool gemm_f32(const GemmArgs& g, bool ta, bool tb, int epi, int batches, hipStream_t s);
+// The same (GEMM_STORE, one batch) with K split where the output has too few
+// tiles for the device: partial products in ws (ws_elems floats), added in a
+// fixed order.
+bool gemm_f32_splitk(const GemmArgs& g, bool ta, bool tb, float* ws, int64_t ws_elems,
+                     hipStream_t s);
 
 // C[m][n] = sum_k A[m][k] B[n][k] (FP32 result) on BF16 MFMA from operands
 // pre-split into BF16 high and low parts, K-contiguous (hi*hi + hi*lo +

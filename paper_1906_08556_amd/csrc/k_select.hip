@@ -1220,7 +1220,7 @@ bool launch_selector_grad(ivx_ctx* ctx, const float* X, int64_t F, const int64_t
   k_train_gather<<<256, 256, 0, s>>>(X, D, fidx, B, F, S.mean, S.istd, S.xs, ctx->dev_err);
   bool ok = true;
   auto gemm = [&](const float* A, int64_t lda, bool ta, const float* Bm, int64_t ldb, bool tb,
-                  float* Cm, int64_t ldc, int M, int N, int K) {
+                  float* Cm, int64_t ldc, int M, int N, int K, bool split = true) {
     GemmArgs g;
     g.A = A;
     g.B = Bm;
@@ -1231,14 +1231,17 @@ bool launch_selector_grad(ivx_ctx* ctx, const float* X, int64_t F, const int64_t
     g.M = M;
     g.N = N;
     g.K = K;
-    ok = ok && gemm_f32(g, ta, tb, GEMM_STORE, 1, s);
+    ok = ok && (split ? gemm_f32_splitk(g, ta, tb, S.gws, S.gws_elems, s)
+                      : gemm_f32(g, ta, tb, GEMM_STORE, 1, s));
   };
-  // forward: a1 = xs W1^T + b1, h1 = relu(a1), ...
-  gemm(S.xs, D, false, P + S.oW1, D, true, S.a1, H1, B, H1, D);
+  // forward: a1 = xs W1^T + b1, h1 = relu(a1), ...; its sums are not split (an
+  // activation at rounding distance from zero would change sides, and with it
+  // the gradient, by 2e-4)
+  gemm(S.xs, D, false, P + S.oW1, D, true, S.a1, H1, B, H1, D, false);
   k_bias_act<<<512, 256, 0, s>>>(S.a1, B, H1, P + S.ob1, 1, S.h1);
-  gemm(S.h1, H1, false, P + S.oW2, H1, true, S.a2, H2, B, H2, H1);
+  gemm(S.h1, H1, false, P + S.oW2, H1, true, S.a2, H2, B, H2, H1, false);
   k_bias_act<<<512, 256, 0, s>>>(S.a2, B, H2, P + S.ob2, 1, S.h2);
-  gemm(S.h2, H2, false, P + S.oW3, H2, true, S.z, C, B, C, H2);
+  gemm(S.h2, H2, false, P + S.oW3, H2, true, S.z, C, B, C, H2, false);
   k_bias_act<<<1024, 256, 0, s>>>(S.z, B, C, P + S.ob3, 0, nullptr);
   k_softmax_xent<<<(B + 3) / 4, 256, 0, s>>>(S.z, B, C, F, fidx, post_idx, post_val, S.dz,
                                              S.loss_part);

@@ -134,6 +134,7 @@ __global__ void k_reduce_b(const float* __restrict__ part, int nsplit, int64_t s
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i >= U * R) return;
   double s = p[i % R];
+#pragma unroll 8
   for (int k = 0; k < nsplit; ++k) s += part[k * sstride + i];
   b[i] = (float)s;
 }
