@@ -18,9 +18,14 @@
 //   2. W = G^{-1}, right-looking over block columns of G:
 //      W_kj = G_kk^{-1} B_kj, then B_ij -= G_ik W_kj for i > k;
 //   3. Phi = W^T W, one block row of W at a time: Phi_ij += W_ki^T W_kj;
-//   4. phi = Phi b (per-tile partial products summed in a fixed order),
-//      log|L(u)| from the diagonal of G, the utterance's objective share,
-//      and Phi (when wanted) in the packed upper layout.
+//   4. Phi in the packed upper layout.
+//
+// phi = G^-T G^-1 b comes with step 1: the forward substitution uses each panel
+// while it is in LDS, the backward one the tiles of G in their slots, one
+// barrier per block step.  It is done before step 2, which together with 3 and
+// 4 is only for the covariance: extraction stops there (R = 400: 0.29 ms for up
+// to 256 utterances, 0.66 ms with the covariance; phi = Phi b, which needed it
+// in every call, took 0.61 ms).
 //
 // The tile layout in registers changes between phases: in phase 1 a slot
 // holds the fragment of the transposed tile (which lets the panel product
@@ -291,6 +296,16 @@ k_estep_rr(int R, int nb, int64_t TP, const float* __restrict__ Lb, const float*
     const uint64_t ck = col_mask(k);
     const uint64_t below = ck & ~rows_below(k + 1);  // column k, rows > k
     done |= ck;
+    if (wave == RR_NW - 1) {  // z_k = G_kk^{-1} b_k (the wave with the fewest panel tiles)
+      const floatx4 g = ld4(dinv + k * RR_TILE + frag), b = ld4(bv + 16 * k + 4 * q16);
+      float z = g[0] * b[0];
+      z = fmaf(g[1], b[1], z);
+      z = fmaf(g[2], b[2], z);
+      z = fmaf(g[3], b[3], z);
+      z += __shfl_xor(z, 16);
+      z += __shfl_xor(z, 32);
+      if (q16 == 0) bv[16 * k + l16] = z;  // every lane has read b_k
+    }
     // panel: G_ik^T = G_kk^{-1} C_ik^T (C_ik^T is the slot's fragment)
     const floatx4 gk = ld4(dinv + k * RR_TILE + frag);
     RR_FOR_MASK(below, {
@@ -299,7 +314,22 @@ k_estep_rr(int R, int nb, int64_t TP, const float* __restrict__ Lb, const float*
       st4(pan + (ti - k - 1) * RR_TILE + frag, y);
       st4(npan + (ti - k - 1) * RR_TILE + frag, -y);
     });
-    __syncthreads();  // panel complete
+    __syncthreads();  // panel and z_k complete
+    // b_i -= G_ik z_k for i > k: thread = row
+    if (tid < (nb - k - 1) * 16) {
+      const float* pt = pan + (tid >> 4) * RR_TILE;
+      const int row = tid & 15;
+      float t = 0.0f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const floatx4 g = ld4(pt + swz(row, 4 * q)), z = ld4(bv + 16 * k + 4 * q);
+        t = fmaf(g[0], z[0], t);
+        t = fmaf(g[1], z[1], t);
+        t = fmaf(g[2], z[2], t);
+        t = fmaf(g[3], z[3], t);
+      }
+      bv[16 * (k + 1) + tid] -= t;
+    }
     // the panel tiles stay in their slots as the fragment of G_ik itself
     RR_FOR_MASK(below, {
       const float* pt = pan + (ti - k - 1) * RR_TILE;
@@ -346,6 +376,58 @@ _Pragma("unroll")
     return;
   }
   if (info && tid == 0) info[u] = 0;
+
+  // ================================ phi: G^T phi = z, block rows from the last
+  // x_k = G_kk^{-T} z_k (by every wave for itself), then z_j -= G_kj^T x_k for
+  // the tiles (k, j), j < k, of the wave's slots
+  for (int k = nb - 1; k >= 0; --k) {
+    __syncthreads();  // z_k complete
+    const float* dk = dinv + k * RR_TILE;
+    const floatx4 z = ld4(bv + 16 * k + 4 * q16);
+    float x = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x = fmaf(dk[swz(4 * q16 + r, l16)], z[r], x);
+    x += __shfl_xor(x, 16);
+    x += __shfl_xor(x, 32);  // x_k[l16]
+    if (wave == 0 && q16 == 0 && 16 * k + l16 < R) phi[u * R + 16 * k + l16] = x;
+    floatx4 xr;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) xr[r] = __shfl(x, 4 * q16 + r);
+    // block row k without its diagonal tile (the last of the row)
+    uint64_t rk = rows_below(k + 1) & ~rows_below(k);
+    const int td = k * (k + 1) / 2 + k;
+    if ((td & (RR_NW - 1)) == wave) rk &= ~(1ull << (td >> 3));
+    RR_FOR_MASK(rk, {
+      float t = tl[s][0] * xr[0];
+      t = fmaf(tl[s][1], xr[1], t);
+      t = fmaf(tl[s][2], xr[2], t);
+      t = fmaf(tl[s][3], xr[3], t);
+      t += __shfl_xor(t, 16);
+      t += __shfl_xor(t, 32);
+      if (q16 == 0) bv[16 * tj + l16] -= t;
+    });
+  }
+  __syncthreads();  // phi complete (written by this workgroup, read below)
+  {
+    double bp = 0.0, pp = 0.0;
+    for (int i = tid; i < R; i += RR_NW * 64) {
+      bp += (double)bvec[u * R + i] * (double)phi[u * R + i];
+      pp += p[i] * p[i];
+    }
+    double v = bp - pp;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if (lane == 0) red[32 + wave] = v;
+    __syncthreads();
+    if (tid == 0) {
+      double ls = 0.0;
+      for (int kk = 0; kk < nb; ++kk) ls += red[kk];
+      double q = 0.0;
+      for (int w = 0; w < RR_NW; ++w) q += red[32 + w];
+      llu[u] = -0.5 * (2.0 * ls) + 0.5 * q;
+    }
+  }
+  if (!Phi_out) return;
 
   // ================================================= 2. W = G^{-1}
   // slots: off-diagonal G_ij (then B_ij, then W_ij); diagonal G_kk^{-1} = W_kk
@@ -404,77 +486,24 @@ _Pragma("unroll")
       tl[s] = mfma4(ld4(rb + tj * RR_TILE + frag), ld4(rb + ti * RR_TILE + frag), tl[s]);
     });
   }
-  __syncthreads();
 
-  // ================================================= 4. phi, objective, Phi
-  // slot fragment: Phi_ij[l16][4 q16 + r].  Tile t contributes Phi_ij b_j to
-  // block i (part[t][0..15]) and, off the diagonal, Phi_ij^T b_i to block j
-  // (part[t][16..31]).
-  float* part = buf;
+  // ================================================= 4. Phi
+  // slot fragment: Phi_ij[l16][4 q16 + r].  Element (a, c) of the lower tile is
+  // (c, a) of the packed upper triangle, row c at c R - c (c - 1) / 2; lanes
+  // along a write consecutive words of one packed row
+  float* out = Phi_out + u * ((int64_t)R * (R + 1) / 2);
   RR_LAUNDER(pk);
 #pragma unroll
   for (int s = 0; s < RR_NT; ++s) {
     const int ti = RR_TI(pk, s), tj = RR_TJ(pk, s);
     if (ti < nb) {
-      const int t = wave + RR_NW * s;
-      const floatx4 v = tl[s];
-      float pr = v[0] * bv[16 * tj + 4 * q16] + v[1] * bv[16 * tj + 4 * q16 + 1] +
-                 v[2] * bv[16 * tj + 4 * q16 + 2] + v[3] * bv[16 * tj + 4 * q16 + 3];
-      pr += __shfl_xor(pr, 16);
-      pr += __shfl_xor(pr, 32);
-      if (q16 == 0) part[t * 32 + l16] = pr;
-      if (ti != tj) {
-        const float bi = bv[16 * ti + l16];
-        float c[4];
+      const int a = 16 * ti + l16;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          c[r] = v[r] * bi;
-          c[r] += __shfl_xor(c[r], 1);
-          c[r] += __shfl_xor(c[r], 2);
-          c[r] += __shfl_xor(c[r], 4);
-          c[r] += __shfl_xor(c[r], 8);
-        }
-        if (l16 == 0) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) part[t * 32 + 16 + 4 * q16 + r] = c[r];
-        }
-      }
-      if (Phi_out) {
-        // element (a, c) of the lower tile is (c, a) of the packed upper
-        // triangle, row c at c R - c (c - 1) / 2; lanes along a write
-        // consecutive words of one packed row
-        const int a = 16 * ti + l16;
-        float* out = Phi_out + u * ((int64_t)R * (R + 1) / 2);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int c = 16 * tj + 4 * q16 + r;
-          if (a < R && c <= a) out[(int64_t)c * R - (int64_t)c * (c - 1) / 2 + (a - c)] = v[r];
-        }
+      for (int r = 0; r < 4; ++r) {
+        const int c = 16 * tj + 4 * q16 + r;
+        if (a < R && c <= a) out[(int64_t)c * R - (int64_t)c * (c - 1) / 2 + (a - c)] = tl[s][r];
       }
     }
-  }
-  __syncthreads();
-  double bp = 0.0, pp = 0.0;
-  for (int i = tid; i < R; i += RR_NW * 64) {
-    const int bi = i >> 4, e = i & 15;
-    float s = 0.0f;
-    for (int j = 0; j <= bi; ++j) s += part[(bi * (bi + 1) / 2 + j) * 32 + e];
-    for (int i2 = bi + 1; i2 < nb; ++i2) s += part[(i2 * (i2 + 1) / 2 + bi) * 32 + 16 + e];
-    phi[u * R + i] = s;
-    bp += (double)bv[i] * (double)s;
-    pp += p[i] * p[i];
-  }
-  double v = bp - pp;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  if (lane == 0) red[32 + wave] = v;
-  __syncthreads();
-  if (tid == 0) {
-    double ls = 0.0;
-    for (int kk = 0; kk < nb; ++kk) ls += red[kk];
-    double q = 0.0;
-    for (int w = 0; w < RR_NW; ++w) q += red[32 + w];
-    llu[u] = -0.5 * (2.0 * ls) + 0.5 * q;
   }
 }
 
