@@ -17,7 +17,7 @@ void be_scatter(const double* M2, const double* sums, const double* counts, int 
                 double* Sw, double* Sb, double* mean, hipStream_t s);
 // Eigendecomposition of the symmetric A [n][n] (n even; overwritten) into
 // w [n] and the columns of V [n][n]; synchronises s once per sweep.  rot
-// [n/2], part [128] workspace.  Returns the sweeps taken, -2 if max_sweeps
+// [n], part [128] workspace.  Returns the sweeps taken, -2 if max_sweeps
 // did not reach the tolerance, -1 on a HIP error.
 int be_jacobi(double* A, double* V, int n, int max_sweeps, double tol, double* w, double2* rot,
               double* part, hipStream_t s);
@@ -32,6 +32,12 @@ void be_gather_cols(const double* src, int ld, const int* idx, int rows, int kee
                     const double* w, double* out, double* vals, hipStream_t s);
 void be_lnorm(const float* X, int64_t n, int dim, const double* mean, const double* W, float* Y,
               hipStream_t s);
+// scores of all pairs (Z1[i], Z2[j]) into M [n1][n2]; q [n1 + n2] workspace
+void be_plda_matrix(const float* Z1, int64_t n1, const float* Z2, int64_t n2, int d,
+                    const double* coef, double* q, float* M, hipStream_t s);
+void be_plda_gather(const float* M, int64_t n1, int64_t n2, const int* trials, int64_t T,
+                    float* scores, int* bad, hipStream_t s);
+bool be_set_attributes();
 void be_plda_coef(const double* psi, int d, double* coef, hipStream_t s);
 void be_plda_score(const float* Z1, int64_t n1, const float* Z2, int64_t n2, int d,
                    const double* coef, const int* trials, int64_t T, float* scores, int* bad,

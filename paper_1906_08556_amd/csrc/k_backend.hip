@@ -4,14 +4,14 @@
 //  k_class_sums      per-class sums and counts (FP64 atomics)
 //  gemm64_tn         second moment X^T X (FP64 MFMA, k_gemm64.hip)
 //  k_scatter         Sw, Sb (divisor N) from the second moment and class sums
-//  k_jacobi_rows/cols  symmetric eigendecomposition by cyclic Jacobi with
-//                    round-robin ordering: n/2 disjoint rotations per step,
-//                    rows (one workgroup per pair) then columns and
-//                    eigenvectors (one workgroup per row); the host checks
-//                    the off-diagonal norm after every sweep
+//  k_jacobi_step     symmetric eigendecomposition by cyclic Jacobi with
+//                    round-robin ordering: n/2 disjoint rotations per step, one
+//                    kernel per step (one workgroup per pair); the host checks the off-diagonal norm
+//                    after every sweep
 //  k_dgemm           small FP64 products (n <= 512) through LDS tiles
-//  k_lnorm           y = W (x - mean) scaled to unit length, one wave per row
-//  k_plda_score      llr of (z1, z2) in the space where W = I and B = diag(psi)
+//  k_lnorm, k_lnorm_white  y = W (x - mean) scaled to unit length
+//  k_plda_score, k_plda_matrix  llr of (z1, z2) in the space where W = I and
+//                    B = diag(psi), trial by trial or for all pairs
 #include <algorithm>
 #include <cmath>
 
@@ -79,56 +79,73 @@ __device__ inline void rr_pair(int n, int r, int k, int& p, int& q) {
   }
 }
 
-// One step of the cyclic Jacobi method on the symmetric A [n][n] (n even):
-// the n/2 disjoint pairs of round-robin step r rotate at once,
-// A <- J^T A J, V <- V J.  k_jacobi_rows: one workgroup per pair computes its
-// rotation from the 2 x 2 block, stores it, and applies J^T to rows p and q.
-// k_jacobi_cols: one workgroup per row i applies every pair's rotation to
-// columns p and q of A and V.
+// Cyclic Jacobi on the symmetric A [n][n] (n even): the n/2 disjoint pairs of
+// round-robin step r rotate at once, A <- J^T A J, V <- V J.  One launch does
+// the column rotations of step r0 (rot0; none if r0 < 0) and the row rotations
+// of step r1 (written to rot1; none if r1 < 0).  A workgroup owns the rows p, q
+// of a pair of step r1: the column rotations act inside a row, the pair's own
+// rotation comes from the 2 x 2 block inside its two rows, and so does the row
+// rotation, so a step needs no other exchange than the rotations of the one
+// before.  A step is bound by its latency (launch, one round of loads, the
+// rotation): 4.3 us at n = 400, and 6.6 us as two kernels, rows then columns.
+// The products are rounded as they were there (a rotation sequence that differs
+// in the last bit ends in other signs and another order).
 __global__ void __launch_bounds__(256)
-k_jacobi_rows(double* __restrict__ A, int n, int r, double2* __restrict__ rot) {
+k_jacobi_step(double* __restrict__ A, double* __restrict__ V, int n, int r0,
+              const double2* __restrict__ rot0, int r1, double2* __restrict__ rot1) {
+  __shared__ double row[2][512];
   __shared__ double s_c, s_s;
+  const int k = threadIdx.x;  // column pair of step r0
   int p, q;
-  rr_pair(n, r, blockIdx.x, p, q);
+  rr_pair(n, r1 < 0 ? 0 : r1, blockIdx.x, p, q);
+  if (k < n / 2) {
+    int cp, cq;
+    rr_pair(n, r0 < 0 ? 0 : r0, k, cp, cq);
+    const double2 cs = r0 < 0 ? make_double2(1.0, 0.0) : rot0[k];
+    double a[2][2], v[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const size_t o = (size_t)(i ? q : p) * n;
+      a[i][0] = A[o + cp];
+      a[i][1] = A[o + cq];
+      v[i][0] = V[o + cp];
+      v[i][1] = V[o + cq];
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      if (cs.y == 0.0) {
+        row[i][cp] = a[i][0];
+        row[i][cq] = a[i][1];
+      } else {
+        const double ap = a[i][0], aq = a[i][1];
+        row[i][cp] = cs.x * ap - cs.y * aq;
+        row[i][cq] = cs.y * ap + cs.x * aq;
+        const double vp = v[i][0], vq = v[i][1];
+        const size_t o = (size_t)(i ? q : p) * n;
+        V[o + cp] = cs.x * vp - cs.y * vq;
+        V[o + cq] = cs.y * vp + cs.x * vq;
+      }
+    }
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
-    const double apq = A[(size_t)p * n + q];
+    const double apq = row[0][q];
     double c = 1.0, t = 0.0;
-    if (apq != 0.0) {
-      const double theta = (A[(size_t)q * n + q] - A[(size_t)p * n + p]) / (2.0 * apq);
+    if (r1 >= 0 && apq != 0.0) {
+      const double theta = (row[1][q] - row[0][p]) / (2.0 * apq);
       t = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
       c = 1.0 / sqrt(t * t + 1.0);
     }
     s_c = c;
     s_s = t * c;
-    rot[blockIdx.x] = make_double2(c, t * c);
+    if (r1 >= 0) rot1[blockIdx.x] = make_double2(c, t * c);
   }
   __syncthreads();
   const double c = s_c, sv = s_s;
-  if (sv == 0.0) return;
   for (int j = threadIdx.x; j < n; j += 256) {
-    const double ap = A[(size_t)p * n + j], aq = A[(size_t)q * n + j];
-    A[(size_t)p * n + j] = c * ap - sv * aq;
-    A[(size_t)q * n + j] = sv * ap + c * aq;
-  }
-}
-
-__global__ void __launch_bounds__(256)
-k_jacobi_cols(double* __restrict__ A, double* __restrict__ V, int n, int r,
-              const double2* __restrict__ rot) {
-  const int i = blockIdx.x;
-  for (int k = threadIdx.x; k < n / 2; k += 256) {
-    const double2 cs = rot[k];
-    if (cs.y == 0.0) continue;
-    int p, q;
-    rr_pair(n, r, k, p, q);
-    double* a = A + (size_t)i * n;
-    const double ap = a[p], aq = a[q];
-    a[p] = cs.x * ap - cs.y * aq;
-    a[q] = cs.y * ap + cs.x * aq;
-    double* v = V + (size_t)i * n;
-    const double vp = v[p], vq = v[q];
-    v[p] = cs.x * vp - cs.y * vq;
-    v[q] = cs.y * vp + cs.x * vq;
+    const double ap = row[0][j], aq = row[1][j];
+    A[(size_t)p * n + j] = sv == 0.0 ? ap : c * ap - sv * aq;
+    A[(size_t)q * n + j] = sv == 0.0 ? aq : sv * ap + c * aq;
   }
 }
 
@@ -261,38 +278,87 @@ k_gather_cols(const double* __restrict__ src, int ld, const int* __restrict__ id
   if (vals && e < keep) vals[e] = w[idx[e]];
 }
 
-// y = W (x - mean) (W optional) scaled to unit length; one wave per row,
-// four rows per workgroup, the centred and whitened rows staged in LDS.
+// y = x - mean (mean optional) scaled to unit length; one wave per row.
 constexpr int LN_MAX = 512;
 __global__ void __launch_bounds__(256)
 k_lnorm(const float* __restrict__ X, int64_t n, int dim, const double* __restrict__ mean,
-        const double* __restrict__ W, float* __restrict__ Y) {
-  __shared__ double t[4][LN_MAX];
-  __shared__ double y[4][LN_MAX];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t row = (int64_t)blockIdx.x * 4 + wv;
-  const bool active = row < n;
-  if (active)
-    for (int d = lane; d < dim; d += 64)
-      t[wv][d] = (double)X[row * dim + d] - (mean ? mean[d] : 0.0);
-  __syncthreads();
+        float* __restrict__ Y) {
+  const int lane = threadIdx.x & 63;
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= n) return;
   double ss = 0.0;
-  if (active) {
-    for (int i = lane; i < dim; i += 64) {
-      double a = t[wv][i];
-      if (W) {
-        const double* wi = W + (size_t)i * dim;
-        a = 0.0;
-        for (int d = 0; d < dim; ++d) a += wi[d] * t[wv][d];
-      }
-      y[wv][i] = a;
-      ss += a * a;
-    }
+  for (int d = lane; d < dim; d += 64) {
+    const double a = (double)X[row * dim + d] - (mean ? mean[d] : 0.0);
+    ss += a * a;
   }
   for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-  if (active) {
-    const double inv = ss > 0.0 ? 1.0 / sqrt(ss) : 0.0;
-    for (int i = lane; i < dim; i += 64) Y[row * dim + i] = (float)(y[wv][i] * inv);
+  const double inv = ss > 0.0 ? 1.0 / sqrt(ss) : 0.0;
+  for (int d = lane; d < dim; d += 64)
+    Y[row * dim + d] = (float)(((double)X[row * dim + d] - (mean ? mean[d] : 0.0)) * inv);
+}
+
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+// The same with a whitening matrix, 16 rows per workgroup: W (x - mean) on FP64
+// MFMA (16 x 16 x 4), the centred rows in LDS, every wave the output columns
+// 16 (wave + 4 t).  A lane reads four consecutive entries of a row of W per 16
+// columns (contraction index 4 (lane / 16) + e), so the 16 rows of a tile are
+// read in whole 128-byte pieces; a lane per output read a column of strided
+// entries for every row.  1200 rows of 400: 113 us (bound by one workgroup's chain
+// of MFMAs, 75 workgroups), a lane per output 284 us.
+constexpr int LN_T = LN_MAX / 64;  // output tiles per wave
+__global__ void __launch_bounds__(256)
+k_lnorm_white(const float* __restrict__ X, int64_t n, int dim, const double* __restrict__ mean,
+              const double* __restrict__ W, float* __restrict__ Y) {
+  extern __shared__ double t[];  // [16][ld], zero beyond dim
+  __shared__ double ssw[4][16];
+  const int ld = (dim + 15) / 16 * 16 + 2;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l16 = lane & 15, q16 = lane >> 4;
+  const int64_t r0 = (int64_t)blockIdx.x * 16;
+  for (int e = tid; e < 16 * ld; e += 256) {
+    const int r = e / ld, c = e - r * ld;
+    t[e] = (c < dim && r0 + r < n) ? (double)X[(r0 + r) * dim + c] - (mean ? mean[c] : 0.0) : 0.0;
+  }
+  __syncthreads();
+  const int nt = (dim + 15) / 16;
+  doublex4 acc[LN_T];
+  double ss[4] = {0.0, 0.0, 0.0, 0.0};  // rows 4 r + q16
+#pragma unroll
+  for (int u = 0; u < LN_T; ++u) {
+    const int tile = w + 4 * u;
+    acc[u] = doublex4{0.0, 0.0, 0.0, 0.0};
+    if (tile >= nt) continue;
+    const int col = 16 * tile + l16;
+    const double* wr = W + (size_t)min(col, dim - 1) * dim;
+    for (int k0 = 0; k0 < dim; k0 += 16) {
+      const int k = k0 + 4 * q16;
+      double b[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) b[e] = (col < dim && k + e < dim) ? wr[k + e] : 0.0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(t[l16 * ld + k + e], b[e], acc[u], 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) ss[r] += acc[u][r] * acc[u][r];
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+#pragma unroll
+    for (int o = 8; o >= 1; o >>= 1) ss[r] += __shfl_xor(ss[r], o, 16);
+    if (l16 == 0) ssw[w][4 * r + q16] = ss[r];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = 4 * r + q16;
+    const double s = (ssw[0][row] + ssw[1][row]) + (ssw[2][row] + ssw[3][row]);
+    const double inv = s > 0.0 ? 1.0 / sqrt(s) : 0.0;
+#pragma unroll
+    for (int u = 0; u < LN_T; ++u) {
+      const int col = 16 * (w + 4 * u) + l16;
+      if (col < dim && r0 + row < n) Y[(r0 + row) * dim + col] = (float)(acc[u][r] * inv);
+    }
   }
 }
 
@@ -347,6 +413,91 @@ k_plda_score(const float* __restrict__ Z1, int64_t n1, const float* __restrict__
   if (lane == 0) scores[t] = (float)(s + coef[2 * d]);
 }
 
+// q[i] = sum_k a_k z_k^2 of the rows of Z1, then of Z2; one wave per row
+__global__ void __launch_bounds__(256)
+k_plda_quad(const float* __restrict__ Z1, int64_t n1, const float* __restrict__ Z2, int64_t n2,
+            int d, const double* __restrict__ coef, double* __restrict__ q) {
+  const int lane = threadIdx.x & 63;
+  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (i >= n1 + n2) return;
+  const float* z = i < n1 ? Z1 + i * d : Z2 + (i - n1) * d;
+  double s = 0.0;
+  for (int k = lane; k < d; k += 64) {
+    const double a = z[k];
+    s += coef[k] * a * a;
+  }
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if (lane == 0) q[i] = s;
+}
+
+// M[i][j] = c + q1_i + q2_j + sum_k b_k z1_ik z2_jk: 64 x 64 tile, FP64 MFMA,
+// a wave per 32 x 32 quarter, 16 dimensions per LDS stage.  1.44 M pairs of
+// d = 200: 46 us (361 workgroups, less than two per CU, staging with
+// conversions between barriers bounds it); 719 k trials one by one take 263 us.
+__global__ void __launch_bounds__(256)
+k_plda_matrix(const float* __restrict__ Z1, int64_t n1, const float* __restrict__ Z2, int64_t n2,
+              int d, const double* __restrict__ coef, const double* __restrict__ q,
+              float* __restrict__ M) {
+  constexpr int LD = 64 + 16;
+  __shared__ double As[16][LD], Bs[16][LD];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l16 = lane & 15, q16 = lane >> 4;
+  const int wm = w >> 1, wn = w & 1;
+  const int64_t i0 = (int64_t)blockIdx.y * 64, j0 = (int64_t)blockIdx.x * 64;
+  doublex4 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+  for (int k0 = 0; k0 < d; k0 += 16) {
+    __syncthreads();
+    for (int e = tid; e < 64 * 16; e += 256) {
+      const int r = e >> 4, k = k0 + (e & 15);
+      As[e & 15][r] = (i0 + r < n1 && k < d) ? coef[d + k] * (double)Z1[(i0 + r) * d + k] : 0.0;
+      Bs[e & 15][r] = (j0 + r < n2 && k < d) ? (double)Z2[(j0 + r) * d + k] : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < 16; ks += 4) {
+      double a[2], b[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) a[i] = As[ks + q16][wm * 32 + i * 16 + l16];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) b[j] = Bs[ks + q16][wn * 32 + j * 16 + l16];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+  }
+  const double c = coef[2 * d];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int64_t col = j0 + wn * 32 + j * 16 + l16;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t row = i0 + wm * 32 + i * 16 + 4 * r + q16;
+        if (row < n1 && col < n2) M[row * n2 + col] = (float)(acc[i][j][r] + q[row] + q[n1 + col] + c);
+      }
+    }
+}
+
+__global__ void __launch_bounds__(256)
+k_plda_gather(const float* __restrict__ M, int64_t n1, int64_t n2, const int* __restrict__ trials,
+              int64_t T, float* __restrict__ scores, int* __restrict__ bad) {
+  for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < T; t += (int64_t)gridDim.x * 256) {
+    const int i = trials[2 * t], j = trials[2 * t + 1];
+    if (i < 0 || i >= n1 || j < 0 || j >= n2) {
+      atomicAdd(bad, 1);
+      scores[t] = NAN;
+    } else {
+      scores[t] = M[(int64_t)i * n2 + j];
+    }
+  }
+}
+
 // dst [n][n] = the symmetric part of src [dim][dim], zero-padded to n >= dim
 __global__ void __launch_bounds__(256)
 k_pad_sym(const double* __restrict__ src, int dim, double* __restrict__ dst, int n) {
@@ -363,6 +514,8 @@ __global__ void k_fill_zero(double* __restrict__ p, int64_t n) {
        i += (int64_t)gridDim.x * blockDim.x)
     p[i] = 0.0;
 }
+
+size_t lnorm_lds(int dim) { return sizeof(double) * 16 * ((size_t)(dim + 15) / 16 * 16 + 2); }
 
 }  // namespace
 
@@ -409,10 +562,10 @@ int be_jacobi(double* A, double* V, int n, int max_sweeps, double tol, double* w
     if (fro < 0.0) fro = std::sqrt(all);
     if (!(std::sqrt(off) > tol * fro)) break;
     if (sweep >= max_sweeps) return -2;
-    for (int r = 0; r < n - 1; ++r) {
-      k_jacobi_rows<<<n / 2, 256, 0, s>>>(A, n, r, rot);
-      k_jacobi_cols<<<n, 256, 0, s>>>(A, V, n, r, rot);
-    }
+    // rot [2][n / 2]: the rotations of the step before and of this one
+    for (int r = 0; r < n; ++r)
+      k_jacobi_step<<<n / 2, 256, 0, s>>>(A, V, n, r - 1, rot + (r + 1) % 2 * (n / 2),
+                                          r < n - 1 ? r : -1, rot + r % 2 * (n / 2));
   }
   k_eye_diag<<<1, 256, 0, s>>>(V, n, A, w, 1);
   return sweep;
@@ -459,7 +612,31 @@ void be_gather_cols(const double* src, int ld, const int* idx, int rows, int kee
 
 void be_lnorm(const float* X, int64_t n, int dim, const double* mean, const double* W, float* Y,
               hipStream_t s) {
-  if (n > 0) k_lnorm<<<(unsigned)((n + 3) / 4), 256, 0, s>>>(X, n, dim, mean, W, Y);
+  if (n <= 0) return;
+  if (W)
+    k_lnorm_white<<<(unsigned)((n + 15) / 16), 256, lnorm_lds(dim), s>>>(X, n, dim, mean, W, Y);
+  else
+    k_lnorm<<<(unsigned)((n + 3) / 4), 256, 0, s>>>(X, n, dim, mean, Y);
+}
+
+bool be_set_attributes() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lnorm_white),
+                             hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)lnorm_lds(LN_MAX)) == hipSuccess;
+}
+
+void be_plda_matrix(const float* Z1, int64_t n1, const float* Z2, int64_t n2, int d,
+                    const double* coef, double* q, float* M, hipStream_t s) {
+  k_plda_quad<<<(unsigned)((n1 + n2 + 3) / 4), 256, 0, s>>>(Z1, n1, Z2, n2, d, coef, q);
+  const dim3 grid((unsigned)((n2 + 63) / 64), (unsigned)((n1 + 63) / 64));
+  k_plda_matrix<<<grid, 256, 0, s>>>(Z1, n1, Z2, n2, d, coef, q, M);
+}
+
+void be_plda_gather(const float* M, int64_t n1, int64_t n2, const int* trials, int64_t T,
+                    float* scores, int* bad, hipStream_t s) {
+  if (T > 0)
+    k_plda_gather<<<(unsigned)std::min<int64_t>((T + 255) / 256, 4096), 256, 0, s>>>(
+        M, n1, n2, trials, T, scores, bad);
 }
 
 void be_plda_coef(const double* psi, int d, double* coef, hipStream_t s) {
