@@ -188,7 +188,7 @@ ivx_status ivx_create(const ivx_dims* dims, int device, ivx_ctx** out) {
   A(dalloc(&c->Wexp, (size_t)c->Cpad * c->Kpad));
   A(dalloc(&c->W16, (size_t)c->Cpad * c->Kpad * 2));
   A(dalloc(&c->linv, C * c->Dp));
-  A(dalloc(&c->linv32r, C * c->Dp));
+  A(dalloc(&c->linv32r, C * c->Dp + 64));  // rows read in pieces of 64
   A(dalloc(&c->ldense, C * 4096));
   A(dalloc(&c->cst, C));
   if (bound_supported(c->C, c->D)) {

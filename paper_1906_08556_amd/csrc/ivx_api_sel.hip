@@ -3,7 +3,6 @@
 // bw_stats and extract_ivectors when they are called with IVX_SEL_LEARNED.
 #include <algorithm>
 #include <cmath>
-#include <vector>
 
 #include "ivx_internal.h"
 
@@ -28,7 +27,7 @@ void selector_free(ivx_ctx* ctx) {
 void presel_free(ivx_ctx* ctx) {
   if (!ctx || !ctx->presel) return;
   Presel* P = ctx->presel;
-  void* ptrs[] = {P->Wd, P->pairs, P->prop, P->score, P->thr, P->lscore, P->hist, P->coff,
+  void* ptrs[] = {P->Wd, P->prop, P->score, P->thr, P->lscore, P->hist, P->coff,
                   P->ent};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);  // teardown
@@ -231,7 +230,6 @@ ivx_status ivx_pruned_set(ivx_ctx* ctx, int32_t k, float prune, void* stream) {
   bool ok = true;
   auto A = [&](bool r) { ok = ok && r; };
   A(salloc(&P->Wd, (int64_t)P->Kd8 * Cpad));
-  A(salloc(&P->pairs, P->Kd8));
   A(salloc(&P->prop, maxF * k));
   A(salloc(&P->score, maxF * k));
   A(salloc(&P->thr, maxF));
@@ -244,18 +242,6 @@ ivx_status ivx_pruned_set(ivx_ctx* ctx, int32_t k, float prune, void* stream) {
     (void)hipGetLastError();
     set_error("ivx_pruned_set: device allocation failed");
     return IVX_ENOMEM;
-  }
-  // feature pairs (a | b << 8) over x~ = [1, x']: (0,0), (0,d), (d,d)
-  std::vector<uint16_t> pr(P->Kd8, 0);
-  for (int d = 1; d <= D; ++d) {
-    pr[d] = (uint16_t)(0 | (d << 8));
-    pr[D + d] = (uint16_t)(d | (d << 8));
-  }
-  if (hipMemcpy(P->pairs, pr.data(), sizeof(uint16_t) * P->Kd8, hipMemcpyHostToDevice) !=
-      hipSuccess) {
-    presel_free(ctx);
-    set_error("ivx_pruned_set: upload failed");
-    return IVX_EDEVICE;
   }
   return IVX_OK;
 }

@@ -135,7 +135,6 @@ struct Presel {
   float margin = 0.0f;
   int Kd8 = 0;              // 1 + 2D features rounded up to 8
   float* Wd = nullptr;      // [Kd8/8][Cpad][8] diagonal coefficients, chunk-major
-  uint16_t* pairs = nullptr;  // [Kd8] feature index pairs (1, x_d, x_d^2)
   int* prop = nullptr;      // [maxF][k]
   float* score = nullptr;   // [maxF][k]
   float* thr = nullptr;     // [maxF] the frame's best filter score minus the margin

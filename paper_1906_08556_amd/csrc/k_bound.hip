@@ -672,9 +672,13 @@ __device__ inline float unordered(int i) { return __int_as_float(i >= 0 ? i : i 
 // pairs of the component (rows 32..63 over all columns, rows 0..31 over
 // columns 0..31: 46 MFMAs).  First pass (score null): the frame's M.  Second
 // pass: the pair's score, and the frame's maximum as an ordered integer.
-// (With one pair per lane and L_c^-1 through the scalar cache the waits for
-// the scalar loads took 9.4 ms for 20M pairs.)
-__global__ void __launch_bounds__(256)
+// A wave takes a contiguous range and loads the rows of the next run while it
+// scores this one; the ranges fill the device once (2 workgroups per CU).  4 M
+// frames, 20 M pairs: 0.9 ms on average for the two passes, near the FP32 MFMA
+// time; 3.8 ms when each run's rows were loaded, under guards, after the run
+// was known, and 9.4 ms with a pair per lane and L_c^-1 through the scalar cache.
+template <bool V4>  // rows of X in whole float4
+__global__ void __launch_bounds__(256, 2)
 k_bound_quad(const float* __restrict__ X, int D, const int* __restrict__ coff, int C,
              const int2* __restrict__ ent, int64_t cap, const double* __restrict__ mu,
              const float* __restrict__ lquad, const double* __restrict__ cst,
@@ -682,22 +686,46 @@ k_bound_quad(const float* __restrict__ X, int D, const int* __restrict__ coff, i
   const int lane = threadIdx.x & 63, h = lane >> 5, l32 = lane & 31;
   const int64_t total = min((int64_t)coff[C], cap);
   const int64_t nw = (int64_t)gridDim.x * 4;
-  // 64 pairs per wave and pass, fewer where they would leave waves idle
-  const int chunk = (int)max<int64_t>(8, min<int64_t>(64, (total + nw - 1) / nw));
+  const int64_t per = max<int64_t>(8, (total + nw - 1) / nw);
+  int64_t e0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * per;
+  const int64_t b1 = min(total, e0 + per);
+  if (e0 >= b1) return;
   int cur = -1;
   float4 a1[8], a0[4];  // rows l32 + 32 and l32, columns 4 (2 s + h) .. + 3
-  float m[32];          // mu at the same columns
+  __shared__ float4 ms[4][16];  // mu_c of the wave
+  const int wave = threadIdx.x >> 6;
   float cc = 0.0f;
   const float4 z4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  for (int64_t e0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * chunk; e0 < total;
-       e0 += nw * chunk) {
-    const int ne = (int)min<int64_t>(chunk, total - e0);
-    const int2 mine = lane < ne ? ent[e0 + lane] : make_int2(0, -1);
-    int pos = 0;
-    while (pos < ne) {
-      const int c = __builtin_amdgcn_readlane(mine.y, pos);
-      const uint64_t same = __ballot(mine.y == c && lane >= pos);
-      const int n = min(32, (int)__popcll(same));  // sorted: a run from pos
+  // a row's columns 4 (2 s + h) + e; beyond D any value of the row, L_c^-1 is
+  // zero there
+  auto row = [&](int g, float4* x) {
+    const float* xp = X + (int64_t)g * D;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const int k = 4 * (2 * s + h);
+      if (V4)
+        x[s] = *reinterpret_cast<const float4*>(xp + min(k, D - 4));
+      else
+        x[s] = make_float4(xp[min(k, D - 1)], xp[min(k + 1, D - 1)], xp[min(k + 2, D - 1)],
+                           xp[min(k + 3, D - 1)]);
+    }
+  };
+  // the 64 entries from e0 are at hand, so the rows of the next run of pairs
+  // are loaded while this one is scored
+  int2 win = ent[min(e0 + lane, b1 - 1)];
+  float4 x[8], xn[8];
+  row(__shfl(win.x, l32), x);
+  while (true) {
+    const int c = __builtin_amdgcn_readfirstlane(win.y);
+    const uint64_t same = __ballot(win.y == c && e0 + lane < b1);
+    const int n = min(32, (int)__popcll(same));  // sorted: a run from e0
+    const int g = __shfl(win.x, l32);
+    const bool more = e0 + n < b1;
+    if (more) {
+      row(__shfl(win.x, n + l32), xn);
+      win = ent[min(e0 + n + lane, b1 - 1)];
+    }
+    {
       if (c != cur) {
         cur = c;
         const float4* Lq = reinterpret_cast<const float4*>(lquad) + (size_t)c * 1024 + l32;
@@ -705,25 +733,16 @@ k_bound_quad(const float* __restrict__ X, int D, const int* __restrict__ coff, i
         for (int s = 0; s < 8; ++s) a1[s] = Lq[(2 * s + h) * 64 + 32];
 #pragma unroll
         for (int s = 0; s < 4; ++s) a0[s] = Lq[(2 * s + h) * 64];
-#pragma unroll
-        for (int s = 0; s < 8; ++s)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int k = 4 * (2 * s + h) + e;
-            m[4 * s + e] = k < D ? (float)mu[(size_t)c * D + k] : 0.0f;
-          }
+        reinterpret_cast<float*>(ms[wave])[lane] = (float)mu[(size_t)c * D + min(lane, D - 1)];
+        __builtin_amdgcn_wave_barrier();
         cc = (float)cst[c];
       }
-      const int g = __shfl(mine.x, pos + (l32 < n ? l32 : 0));
-      const float* xp = X + (int64_t)g * D;
       float4 d[8];
 #pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        const int k = 4 * (2 * s + h);
-        d[s].x = k < D ? xp[k] - m[4 * s] : 0.0f;
-        d[s].y = k + 1 < D ? xp[k + 1] - m[4 * s + 1] : 0.0f;
-        d[s].z = k + 2 < D ? xp[k + 2] - m[4 * s + 2] : 0.0f;
-        d[s].w = k + 3 < D ? xp[k + 3] - m[4 * s + 3] : 0.0f;
+      for (int s = 0; s < 8; ++s)
+        {
+        const float4 m = ms[wave][2 * s + h];
+        d[s] = make_float4(x[s].x - m.x, x[s].y - m.y, x[s].z - m.z, x[s].w - m.w);
       }
       floatx16 y1 = floatx16{0}, y0 = floatx16{0};
 #pragma unroll
@@ -745,14 +764,17 @@ k_bound_quad(const float* __restrict__ X, int D, const int* __restrict__ coff, i
       if (h == 0 && l32 < n) {
         const float sv = cc - 0.5f * q;
         if (score) {
-          score[e0 + pos + l32] = sv;
+          score[e0 + l32] = sv;
           atomicMax(reinterpret_cast<int*>(Mf) + g, ordered(sv));
         } else {
           Mf[g] = sv;
         }
       }
-      pos += n;
     }
+    if (!more) break;
+    e0 += n;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) x[s] = xn[s];
   }
 }
 
@@ -1002,7 +1024,7 @@ void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipS
   const int64_t t2 = (F + 511) / 512, t1 = (F + 255) / 256;
   const bool two = 2.0 * (double)((t2 + slots - 1) / slots) <= 1.3 * (double)((t1 + slots - 1) / slots);
   const unsigned nblk = (unsigned)std::min<int64_t>(two ? t2 : t1, slots);
-  const unsigned nq = (unsigned)std::min<int64_t>((F + 31) / 32, 8 * (int64_t)ctx->ncu);
+  const unsigned nq = (unsigned)std::min<int64_t>((F + 31) / 32, 2 * (int64_t)ctx->ncu);
   const unsigned ne = (unsigned)std::min<int64_t>((F + 63) / 64, 8 * (int64_t)ctx->ncu);
   ProfScope ps(ctx, PK_FRAME_SELECT, s);
   k_bound_frames<<<n16, 256, 0, s>>>(X, F, ctx->D, ctx->shift, Fdev, xh, tg);
@@ -1011,8 +1033,9 @@ void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipS
   k_best_hist<<<nb, 256, ldsc, s>>>(F, fpb, ctx->C, ctx->cflag, Fdev, ctx->hist);
   launch_hist_scan((int)nb, ctx->C, ctx->hist, ctx->coff, s);
   k_best_scatter<<<nb, 256, ldsc, s>>>(F, fpb, ctx->C, ctx->cflag, Fdev, ctx->hist, ctx->coff, ent1);
-  k_bound_quad<<<nq, 256, 0, s>>>(X, ctx->D, ctx->coff, ctx->C, ent1, F, ctx->mu, ctx->lquad,
-                                  ctx->cst, nullptr, ctx->cM);
+  const bool v4 = ctx->D % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
+  (v4 ? k_bound_quad<true> : k_bound_quad<false>)<<<nq, 256, 0, s>>>(
+      X, ctx->D, ctx->coff, ctx->C, ent1, F, ctx->mu, ctx->lquad, ctx->cst, nullptr, ctx->cM);
   (two ? k_bound_list<2> : k_bound_list<1>)<<<nblk, 64 * BW, 0, s>>>(
       xh, tg, F, ctx->Wf, ctx->cb, ctx->bmax, ctx->Cpad / 2, margin + err - 3.0f, ctx->cM, surv,
       ctx->cflag, Fdev);
@@ -1020,8 +1043,8 @@ void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipS
   launch_hist_scan((int)nb, ctx->C, ctx->hist, ctx->coff, s);
   k_bound_scatter<<<nb, 256, ldsc, s>>>(F, fpb, ctx->C, ctx->cand, ctx->cflag, Fdev, ctx->hist,
                                         ctx->coff, cap, ctx->ent, cMi);
-  k_bound_quad<<<nq, 256, 0, s>>>(X, ctx->D, ctx->coff, ctx->C, ctx->ent, cap, ctx->mu, ctx->lquad,
-                                  ctx->cst, score, ctx->cM);
+  (v4 ? k_bound_quad<true> : k_bound_quad<false>)<<<nq, 256, 0, s>>>(
+      X, ctx->D, ctx->coff, ctx->C, ctx->ent, cap, ctx->mu, ctx->lquad, ctx->cst, score, ctx->cM);
   k_bound_mark<<<ne, 256, 0, s>>>(ctx->coff, ctx->C, ctx->ent, cap, score, cMi, margin, err,
                                   ctx->cflag);
   k_bound_append<<<ne, 256, 0, s>>>(ctx->coff, ctx->C, ctx->ent, cap, score, cMi, margin, err,

@@ -13,8 +13,8 @@
 //                    top-k (ties to the lower index) and a running log-sum-exp
 // then over all frames:
 //   k_sel_hist / scan / k_sel_scatter   (frame, proposal) pairs by component
-//   k_sel_score      FP32 shifted-form score of every pair: one component per
-//                    wave pass, its L^-1 read through the scalar cache
+//   k_sel_score      FP32 shifted-form score of every pair: 32 pairs of one
+//                    component at a time against L^-1 on the matrix cores
 //   k_sel_thr / k_kept_hist / scan / k_kept_scatter / k_exact_sorted
 //                    FP64 exact scores of the proposals within the margin of
 //                    the frame's best, again bucketed by component
@@ -408,59 +408,89 @@ k_mlp_l3(const __bf16* __restrict__ H2, int64_t rows, int64_t row0, int K,
 //   g = log w_c - D/2 log 2pi - 1/2 sum_d log s^2_cd - 1/2 sum_d mu'^2 / s^2,
 // over the features (1, x'_1..x'_D, x'_1^2..x'_D^2).  Coefficients are stored
 // chunk-major like the full-covariance ones: (c, k) at ((k/8) Cpad + c) 8 + k%8.
-__global__ void k_diag_prepare(const double* __restrict__ w, const double* __restrict__ mu,
-                               const double* __restrict__ cov, const float* __restrict__ shift,
-                               int C, int Cpad, int D, int Kd8, float* __restrict__ Wd) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+// One wave per component, a lane per dimension (a thread per component left the
+// device idle: 80 us at C = 2048, D = 60); g is summed in the order of d.
+__global__ void __launch_bounds__(256)
+k_diag_prepare(const double* __restrict__ w, const double* __restrict__ mu,
+               const double* __restrict__ cov, const float* __restrict__ shift, int C, int Cpad,
+               int D, int Kd8, float* __restrict__ Wd) {
+  __shared__ double ts[4][64];
+  const int wave = threadIdx.x >> 6, d = threadIdx.x & 63;
+  const int c = blockIdx.x * 4 + wave;
   if (c >= Cpad) return;
   auto at = [&](int k) -> float& { return Wd[((size_t)(k >> 3) * Cpad + c) * 8 + (k & 7)]; };
   if (c >= C) {  // padding components: never among the best
-    for (int k = 0; k < Kd8; ++k) at(k) = (k == 0) ? -1e30f : 0.0f;
+    for (int k = d; k < Kd8; k += 64) at(k) = (k == 0) ? -INFINITY : 0.0f;
     return;
   }
-  double g = log(w[c]) - 0.5 * D * 1.8378770664093454836;
-  for (int d = 0; d < D; ++d) {
+  if (d < D) {
     const double s2 = cov[((size_t)c * D + d) * D + d];
     const double m = mu[(size_t)c * D + d] - (double)shift[d];
-    g -= 0.5 * log(s2) + 0.5 * m * m / s2;
+    ts[wave][d] = 0.5 * log(s2) + 0.5 * m * m / s2;
     at(1 + d) = (float)(m / s2);
     at(1 + D + d) = (float)(-0.5 / s2);
   }
-  at(0) = (float)g;
-  for (int k = 1 + 2 * D; k < Kd8; ++k) at(k) = 0.0f;
+  __builtin_amdgcn_wave_barrier();
+  if (d == 0) {
+    double g = log(w[c]) - 0.5 * D * 1.8378770664093454836;
+    for (int i = 0; i < D; ++i) g -= ts[wave][i];
+    at(0) = (float)g;
+  }
+  for (int k = 1 + 2 * D + d; k < Kd8; k += 64) at(k) = 0.0f;
 }
 
 // Diagonal-UBM scores of every (frame, component) on FP32 MFMA and the k best
 // components per frame (ties to the lower index).  One workgroup per 128
 // frames loops over all components 128 at a time (W chunks of 8 features
 // staged through LDS as in k_frame_tile); after each 128-component tile the
-// two lane-halves holding a frame insert the tile's scores that beat their
-// KM-th into a sorted list in registers; at the end the two lists are merged
-// by counting ranks in LDS.  prop[t][0..k): the k best, best first.
+// two lane-halves holding a frame put the tile's scores that beat their KM-th
+// into a queue of DQ in LDS, and when a lane's queue is full all lanes insert
+// theirs into a sorted list in registers (in the queue's order: the list is
+// the one of immediate insertion).  At the end the two lists are merged by
+// counting ranks in LDS.  prop[t][0..k): the k best, best first.
+// Insertions bound it when done score by score: among 64 lanes one almost
+// always inserts, at about 100 instructions.  157 k frames, C = 2048, k = 20:
+// 1261 us, 1771 us with immediate insertion; the FP32 MFMAs alone are 525 us, the
+// vector units' insertions another 350 us that overlap little with two waves per
+// SIMD (lists, features and sums take 240 registers).  
+constexpr int DQ = 20;
 template <int KM>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, KM > 20 ? 1 : 2)
 k_diag_topk(const float* __restrict__ X, int64_t F, int D, const float* __restrict__ shift,
-            const float* __restrict__ Wd, int C, int Cpad, int Kd8,
-            const uint16_t* __restrict__ pairs, int k, int* __restrict__ prop) {
+            const float* __restrict__ Wd, int Cpad, int Kd8, int k, int* __restrict__ prop) {
   constexpr int FR = 32, FTD = 128, CTD = 128, NCBD = CTD / 32, WLDD = 12;
   extern __shared__ float smem[];
-  float* Ws = smem;                                            // [2][CTD][WLDD]
-  float* xs = smem + 2 * CTD * WLDD;                           // [FTD][D+1]
-  uint32_t* prs = reinterpret_cast<uint32_t*>(xs + FTD * (D + 1));
+  float* Ws = smem;                                            // [2][2][CTD][WLDD]
+  float* xs = smem;                                            // first: [FTD][D+1]
   float* lvs = smem;                                           // after the loop: [2][FTD][KM]
   int* lis = reinterpret_cast<int*>(lvs + 2 * FTD * KM);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int h = lane >> 5, l32 = lane & 31;
   const int DS = D + 1;
+  int2* qs = reinterpret_cast<int2*>(smem + 4 * CTD * WLDD) + tid;  // [DQ][256]
   const int64_t f0 = (int64_t)blockIdx.x * FTD;
   const int nq = Kd8 / 8;
-  for (int i = tid; i < Kd8 / 2; i += 256) prs[i] = reinterpret_cast<const uint32_t*>(pairs)[i];
-  for (int i = tid; i < FTD * DS; i += 256) {
-    const int fr = i / DS, a = i - fr * DS;
-    const int64_t g = f0 + fr;
-    float v = (a == 0) ? 1.0f : 0.0f;
-    if (a > 0 && g < F) v = X[g * D + (a - 1)] - shift[a - 1];
-    xs[i] = v;
+  {
+    const float sh = shift[min(lane, D - 1)];
+    float v[FR];  // a frame per wave and step, its 32 loads in flight together
+#pragma unroll
+    for (int i = 0; i < FR; ++i)
+      v[i] = X[min(f0 + wave * FR + i, F - 1) * D + min(lane, D - 1)];
+#pragma unroll
+    for (int i = 0; i < FR; ++i)
+      if (lane < D) xs[(wave * FR + i) * DS + lane] = v[i] - sh;
+  }
+  __syncthreads();
+  // the lane's half of its frame's features (1, x'_1.., x'_1^2..) stays in registers
+  float xf[64];
+  {
+    const float* xw = xs + (wave * FR + l32) * DS;
+#pragma unroll
+    for (int t = 0; t < 64; ++t) {
+      const int kk = 8 * (t >> 2) + 4 * h + (t & 3);
+      const float v = xw[kk <= D ? max(kk - 1, 0) : min(kk - 1 - D, D - 1)];
+      xf[t] = kk == 0 ? 1.0f : kk <= D ? v : kk <= 2 * D ? v * v : 0.0f;
+    }
   }
   float lv[KM];
   int li[KM];
@@ -469,75 +499,101 @@ k_diag_topk(const float* __restrict__ X, int64_t F, int D, const float* __restri
     lv[q] = -INFINITY;
     li[q] = -1;
   }
-  const float* xw = xs + (wave * FR + l32) * DS;
+  int nqd = 0;
+  float thr = -3.402823466e38f;
+  auto drain = [&]() {
+    auto insert = [&](int i) {
+      const int2 en = qs[i * 256];
+      const float v = i < nqd ? __int_as_float(en.x) : -INFINITY;  // -INFINITY: no insertion
+      const int c = en.y;
+#pragma unroll
+      for (int q = KM - 1; q > 0; --q) {
+        const float vp = lv[q - 1], vq = lv[q];
+        const int ip = li[q - 1], iq = li[q];
+        const bool up = v > vp;
+        const bool atq = v > vq;
+        lv[q] = __builtin_amdgcn_fmed3f(v, vp, vq);
+        li[q] = up ? ip : (atq ? c : iq);
+      }
+      li[0] = v > lv[0] ? c : li[0];
+      lv[0] = fmaxf(v, lv[0]);
+    };
+    for (int i = 0; __any(i < nqd); i += 2) {  // DQ is even
+      insert(i);
+      insert(i + 1);
+    }
+    nqd = 0;
+    // above the lane's own KM-th, and not below KM / 2 scores of either half
+    const int own = __float_as_int(lv[KM - 1]);
+    const float up = lv[KM - 1] == -INFINITY ? -3.402823466e38f
+                     : lv[KM - 1] == 0.0f    ? __int_as_float(1)
+                                             : __int_as_float(own >= 0 ? own + 1 : own - 1);
+    const float half = fminf(lv[KM / 2 - 1], __shfl_xor(lv[KM / 2 - 1], 32));
+    thr = fmaxf(up, half);
+  };
   for (int c0 = 0; c0 < Cpad; c0 += CTD) {
-    // two threads stage the 8 coefficients of one component
-    float4 r0;
-    auto gload = [&](int q) {
-      r0 = *reinterpret_cast<const float4*>(Wd + ((size_t)q * Cpad + c0 + (tid >> 1)) * 8 +
-                                             (tid & 1) * 4);
+    // two threads stage the 8 coefficients of one component, 16 features a time
+    const float4* wg = reinterpret_cast<const float4*>(Wd) + (size_t)(c0 + (tid >> 1)) * 2 + (tid & 1);
+    float4 ra, rb;
+    auto gload = [&](int p) {
+      ra = wg[(size_t)min(2 * p, nq - 1) * Cpad * 2];
+      rb = wg[(size_t)min(2 * p + 1, nq - 1) * Cpad * 2];
     };
     auto sstore = [&](int buf) {
-      *reinterpret_cast<float4*>(Ws + (buf * CTD + (tid >> 1)) * WLDD + (tid & 1) * 4) = r0;
+      float* d = Ws + (buf * 2 * CTD + (tid >> 1)) * WLDD + (tid & 1) * 4;
+      *reinterpret_cast<float4*>(d) = ra;
+      *reinterpret_cast<float4*>(d + CTD * WLDD) = rb;
     };
-    __syncthreads();  // the previous tile's stages are consumed
     gload(0);
+    __syncthreads();  // the previous tile's stages (the frames) are consumed
     sstore(0);
     __syncthreads();
     floatx16 acc[NCBD];
 #pragma unroll
     for (int cb = 0; cb < NCBD; ++cb) acc[cb] = floatx16{0};
-    for (int q = 0; q < nq; ++q) {
-      const int cur = q & 1;
-      if (q + 1 < nq) gload(q + 1);
-      const float* wb = Ws + (cur * CTD + l32) * WLDD + 4 * h;
-      float4 wv[NCBD];
 #pragma unroll
-      for (int cb = 0; cb < NCBD; ++cb) wv[cb] = *reinterpret_cast<const float4*>(wb + cb * 32 * WLDD);
-      const uint32_t pw0 = prs[4 * q + 2 * h], pw1 = prs[4 * q + 2 * h + 1];
+    for (int q = 0; q < 16; ++q) {
+      if (q < nq) {
+        const int p = q >> 1;
+        if ((q & 1) == 0) gload(p + 1);
+        const float* wb = Ws + ((p & 1) * 2 * CTD + (q & 1) * CTD + l32) * WLDD + 4 * h;
+        float4 wv[NCBD];
 #pragma unroll
-      for (int s2 = 0; s2 < 4; ++s2) {
-        const uint32_t pr = ((s2 < 2) ? pw0 : pw1) >> ((s2 & 1) * 16);
-        const float bv = xw[pr & 0xff] * xw[(pr >> 8) & 0xff];
+        for (int cb = 0; cb < NCBD; ++cb)
+          wv[cb] = *reinterpret_cast<const float4*>(wb + cb * 32 * WLDD);
 #pragma unroll
-        for (int cb = 0; cb < NCBD; ++cb) {
-          const float av = (s2 == 0) ? wv[cb].x : (s2 == 1) ? wv[cb].y : (s2 == 2) ? wv[cb].z : wv[cb].w;
-          acc[cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[cb], 0, 0, 0);
+        for (int s2 = 0; s2 < 4; ++s2)
+#pragma unroll
+          for (int cb = 0; cb < NCBD; ++cb) {
+            const float av = (s2 == 0) ? wv[cb].x : (s2 == 1) ? wv[cb].y : (s2 == 2) ? wv[cb].z : wv[cb].w;
+            acc[cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, xf[4 * q + s2], acc[cb], 0, 0, 0);
+          }
+        if ((q & 1) == 1 && q + 1 < nq) {
+          sstore((p + 1) & 1);
+          __syncthreads();
         }
       }
-      if (q + 1 < nq) sstore(cur ^ 1);
-      __syncthreads();
     }
-    float tmax = -INFINITY;
+    // one copy of the insertion code per 4 rows, not per score
+#pragma unroll 1
+    for (int cb = 0; cb < NCBD; ++cb) {
+      floatx16 av;
 #pragma unroll
-    for (int cb = 0; cb < NCBD; ++cb)
+      for (int r = 0; r < 16; ++r)
+        av[r] = cb < 2 ? (cb == 0 ? acc[0][r] : acc[1][r]) : (cb == 2 ? acc[2][r] : acc[3][r]);
+      const int cl = c0 + cb * 32 + 4 * h;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, acc[cb][r]);
-    if (tmax > lv[KM - 1]) {
+      for (int r = 0; r < 16; r += 4) {
 #pragma unroll
-      for (int cb = 0; cb < NCBD; ++cb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float v = acc[cb][r];
-          const int c = c0 + cb * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-          if (c < C && v > lv[KM - 1]) {
-#pragma unroll
-            for (int q = KM - 1; q > 0; --q) {
-              const float vp = lv[q - 1], vq = lv[q];
-              const int ip = li[q - 1], iq = li[q];
-              const bool up = v > vp;
-              const bool atq = v > vq;
-              lv[q] = up ? vp : (atq ? v : vq);
-              li[q] = up ? ip : (atq ? c : iq);
-            }
-            if (v > lv[0]) {
-              lv[0] = v;
-              li[0] = c;
-            }
-          }
+        for (int e = 0; e < 4; ++e) {  // written always, counted if it is to stay
+          qs[nqd * 256] = make_int2(__float_as_int(av[r + e]), cl + 2 * r + e);
+          nqd += av[r + e] >= thr ? 1 : 0;
         }
+        if (__any(nqd > DQ - 4)) drain();
+      }
     }
   }
+  drain();
   __syncthreads();  // stages dead: the lists reuse the memory
   const int f = wave * FR + l32;
 #pragma unroll
@@ -668,57 +724,138 @@ k_kept_scatter(int64_t F, int fpb, int k, int C, const int* __restrict__ prop, c
 }
 
 // FP32 shifted-form score cst_c - 1/2 ||L_c^-1 (x - mu_c)||^2 of every
-// (frame, proposal) pair, pairs sorted by component.  The wave handles one
-// component at a time (a wave-uniform index), so mu_c and L_c^-1 (FP32, rows
-// packed: row i holds columns 0..i) come through the scalar cache.  Used only
-// to pick the pairs that get the exact FP64 score.
-__global__ void __launch_bounds__(256)
+// (frame, proposal) pair, pairs sorted by component.  Used only to pick the
+// pairs that get the exact FP64 score.  A wave takes a contiguous range of the
+// pairs, up to 32 of one component at a time (columns) on v_mfma_f32_32x32x2_f32,
+// the rows of L_c^-1 in registers until the component changes (rows 32..63 over
+// 64 columns, rows 0..31 over 32: 48 MFMAs).  The matrix cores add the products
+// one by one in the order of the columns, and the squares are added row by row,
+// which is the sum a lane per pair would form.  3.1 M pairs at D = 60:
+// 247 us (125 us of MFMA; then the loads of the rows); a lane per pair with L_c^-1
+// through the scalar cache took 1208 us.
+template <bool V4>  // rows of X in whole float4
+__global__ void __launch_bounds__(256, 2)
 k_sel_score(const float* __restrict__ X, int D, int k, const int* __restrict__ coff, int C,
             const int2* __restrict__ ent, int64_t cap, const double* __restrict__ mu,
             const float* __restrict__ linv32r, const double* __restrict__ cst,
             float* __restrict__ score) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t total = coff[C];
-  const bool valid = e < total && e < cap;
-  const int2 en = valid ? ent[e] : make_int2(0, -1);
+  const int lane = threadIdx.x & 63, h = lane >> 5, l32 = lane & 31;
+  const int64_t total = min((int64_t)coff[C], cap);
+  const int64_t nw = (int64_t)gridDim.x * 4;
+  const int64_t per = max<int64_t>(8, (total + nw - 1) / nw);
+  const int wave = threadIdx.x >> 6;
+  int64_t e0 = ((int64_t)blockIdx.x * 4 + wave) * per;
+  const int64_t b1 = min(total, e0 + per);
+  if (e0 >= b1) return;
   const int Dp = D * (D + 1) / 2;
-  bool todo = valid;
-  float my = 0.0f;  // stored after the loop: no store may precede the scalar loads
-  float xr[64];
-  {
-    const float* xp = X + (int64_t)(valid ? en.x / k : 0) * D;
+  __shared__ double ms[4][64];  // mu_c of the wave
+  int cur = -1;
+  float a1[32], a0[16];  // rows l32 + 32 and l32, columns 2 s + h
+  float cc = 0.0f;
+  // a row's columns 4 (2 q + h) + e; beyond D any value of the row, L_c^-1 is
+  // zero there
+  auto row = [&](int slot, float* x) {
+    const float* xp = X + (int64_t)(slot / k) * D;
 #pragma unroll
-    for (int j = 0; j < 64; ++j) xr[j] = (valid && j < D) ? xp[j] : 0.0f;
-  }
-  while (true) {
-    const uint64_t pend = __ballot(todo);
-    if (pend == 0) break;
-    const int src = __ffsll((unsigned long long)pend) - 1;
-    const int cu = __builtin_amdgcn_readfirstlane(__shfl(en.y, src));
-    // every lane computes component cu (uniform control flow keeps the
-    // loads of mu_c and L_c scalar); the lanes that hold it keep the result
-    const double* mc = mu + (size_t)cu * D;
-    const float* L = linv32r + (size_t)cu * Dp;
-    float dv[64];
+    for (int q = 0; q < 8; ++q) {
+      const int j = 4 * (2 * q + h);
+      if (V4) {
+        const float4 v = *reinterpret_cast<const float4*>(xp + min(j, D - 4));
+        x[4 * q] = v.x;
+        x[4 * q + 1] = v.y;
+        x[4 * q + 2] = v.z;
+        x[4 * q + 3] = v.w;
+      } else {
 #pragma unroll
-    for (int j = 0; j < 64; ++j) dv[j] = (j < D) ? (float)((double)xr[j] - mc[j]) : 0.0f;
-    float q = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 64; ++i) {
-      if (i < D) {
-        const float* Li = L + i * (i + 1) / 2;
-        float y = 0.0f;
-#pragma unroll
-        for (int j = 0; j <= i; ++j) y = fmaf(Li[j], dv[j], y);
-        q = fmaf(y, y, q);
+        for (int e = 0; e < 4; ++e) x[4 * q + e] = xp[min(j + e, D - 1)];
       }
     }
-    if (todo && en.y == cu) {
-      todo = false;
-      my = (float)cst[cu] - 0.5f * q;
+  };
+  // the 64 entries from e0 are at hand, so the rows of the next run of pairs
+  // are loaded while this one is scored
+  int2 win = ent[min(e0 + lane, b1 - 1)];
+  float x[32], xn[32];
+  row(__shfl(win.x, l32), x);
+  while (true) {
+    const int c = __builtin_amdgcn_readfirstlane(win.y);
+    const uint64_t same = __ballot(win.y == c && e0 + lane < b1);
+    const int n = min(32, (int)__popcll(same));  // sorted: a run from e0
+    const int slot = __shfl(win.x, l32);
+    const bool more = e0 + n < b1;
+    if (more) {
+      row(__shfl(win.x, n + l32), xn);
+      win = ent[min(e0 + n + lane, b1 - 1)];
     }
+    {
+      if (c != cur) {
+        cur = c;
+        // whole 64-column rows are read: past the diagonal the next rows (the
+        // array ends with 64 entries of padding), replaced by zero
+        const float* L = linv32r + (size_t)c * Dp + h;
+        const int r0 = min(l32, D - 1), r1 = min(l32 + 32, D - 1);
+        const float* L0 = L + r0 * (r0 + 1) / 2;
+        const float* L1 = L + r1 * (r1 + 1) / 2;
+#pragma unroll
+        for (int t = 0; t < 32; ++t) {
+          const int j = 2 * t + h;
+          a1[t] = L1[2 * t];
+          if (!(l32 + 32 < D && j <= r1)) a1[t] = 0.0f;
+          if (t < 16) {
+            a0[t < 16 ? t : 0] = L0[2 * t];
+            if (!(l32 < D && j <= r0)) a0[t < 16 ? t : 0] = 0.0f;
+          }
+        }
+        ms[wave][lane] = mu[(size_t)c * D + min(lane, D - 1)];
+        __builtin_amdgcn_wave_barrier();
+        cc = (float)cst[c];
+      }
+      floatx16 y1 = floatx16{0}, y0 = floatx16{0};
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        __builtin_amdgcn_sched_barrier(0);  // keeps the reads of mu_c out of the registers
+        float d[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          d[e] = (float)((double)x[4 * q + e] - ms[wave][4 * (2 * q + h) + e]);
+        // columns 8 q + 4 h + e to 8 q + 2 e + h: halves exchanged pairwise
+        const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[0]),
+                                                        __float_as_uint(d[1]), false, false);
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(d[2]),
+                                                        __float_as_uint(d[3]), false, false);
+        const float b[4] = {__uint_as_float(p[0]), __uint_as_float(r[0]), __uint_as_float(p[1]),
+                            __uint_as_float(r[1])};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          y1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[4 * q + e], b[e], y1, 0, 0, 0);
+          if (q < 4)
+            y0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[q < 4 ? 4 * q + e : 0], b[e], y0, 0, 0, 0);
+        }
+      }
+      // rows 8 b + 4 h + e at register 4 b + e: the sum passes between the halves
+      float q = 0.0f;
+      auto add_rows = [&](const floatx16& y) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+          for (int hh = 0; hh < 2; ++hh) {
+            float t = q;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t = fmaf(y[4 * b + e], y[4 * b + e], t);
+            // the half whose turn it is hands its sum to both
+            const auto u = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t),
+                                                            false, false);
+            q = __uint_as_float(u[hh]);
+          }
+      };
+      add_rows(y0);
+      if (D > 32) add_rows(y1);
+      if (h == 0 && l32 < n) score[slot] = cc - 0.5f * q;
+    }
+    if (!more) break;
+    e0 += n;
+#pragma unroll
+    for (int t = 0; t < 32; ++t) x[t] = xn[t];
   }
-  if (valid) score[en.x] = my;
 }
 
 // One wave per frame: FP64 exact scores of the proposals within `margin` of
@@ -1029,10 +1166,11 @@ size_t l3_lds_bytes(int km) {
 
 int l3_km(int k) { return k <= 8 ? 8 : (k <= 20 ? 20 : 32); }
 
-size_t diag_lds_bytes(int D, int Kd8, int km) {
-  const size_t stage = sizeof(float) * (2 * 128 * 12 + 128 * (D + 1)) + sizeof(uint16_t) * Kd8;
+size_t diag_lds_bytes(int D, int km) {
+  const size_t stage = sizeof(float) * 4 * 128 * 12 + 256 * DQ * sizeof(int2);
+  const size_t frames = sizeof(float) * 128 * (D + 1);
   const size_t lists = sizeof(float) * 2 * 128 * km * 2;
-  return std::max(stage, lists);
+  return std::max(std::max(stage, frames), lists);
 }
 
 }  // namespace
@@ -1041,13 +1179,13 @@ bool select_set_attributes() {
   bool ok = true;
   ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&k_diag_topk<32>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 (int)diag_lds_bytes(63, 128, 32)) == hipSuccess;
+                                 (int)diag_lds_bytes(63, 32)) == hipSuccess;
   ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&k_diag_topk<20>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 (int)diag_lds_bytes(63, 128, 20)) == hipSuccess;
+                                 (int)diag_lds_bytes(63, 20)) == hipSuccess;
   ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&k_diag_topk<8>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 (int)diag_lds_bytes(63, 128, 8)) == hipSuccess;
+                                 (int)diag_lds_bytes(63, 8)) == hipSuccess;
   ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mlp_l3<8>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize,
                                  (int)l3_lds_bytes(8)) == hipSuccess;
@@ -1119,6 +1257,19 @@ bool launch_selector_mlp(ivx_ctx* ctx, const float* X, int64_t F, uint16_t* h1_o
   return true;
 }
 
+// two workgroups per CU (the registers of k_sel_score allow no more), fewer
+// where a wave would get less than 8 pairs
+static void launch_sel_score(ivx_ctx* ctx, const float* X, int k, const int* coff, const int2* ent,
+                             int64_t cap, float* score, hipStream_t s) {
+  const unsigned nb = (unsigned)std::min<int64_t>((cap + 31) / 32, 2 * (int64_t)ctx->ncu);
+  if (ctx->D % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0)
+    k_sel_score<true><<<nb, 256, 0, s>>>(X, ctx->D, k, coff, ctx->C, ent, cap, ctx->mu,
+                                         ctx->linv32r, ctx->cst, score);
+  else
+    k_sel_score<false><<<nb, 256, 0, s>>>(X, ctx->D, k, coff, ctx->C, ent, cap, ctx->mu,
+                                          ctx->linv32r, ctx->cst, score);
+}
+
 // Exact FP64 scores of the proposals within the margin of each frame's best
 // filter score, bucketed by component and scored by k_exact_sorted (the
 // sort buffers of the filter pass are reused).
@@ -1148,8 +1299,7 @@ void launch_select_learned(ivx_ctx* ctx, const float* X, int64_t F, int prec, in
     launch_hist_scan(nb, ctx->C, S.hist, S.coff, s);
     k_sel_scatter<<<nb, 256, ldsc, s>>>(F, fpb, S.k, ctx->C, S.prop, S.fb, S.hist, S.coff, S.ent);
     const int64_t cap = F * S.k;
-    k_sel_score<<<(unsigned)((cap + 255) / 256), 256, 0, s>>>(
-        X, ctx->D, S.k, S.coff, ctx->C, S.ent, cap, ctx->mu, ctx->linv32r, ctx->cst, S.score);
+    launch_sel_score(ctx, X, S.k, S.coff, S.ent, cap, S.score, s);
     exact_kept(ctx, X, F, S.k, S.prop, S.fb, S.score, S.margin, S.thr, S.hist, S.coff, S.ent,
                S.lscore, s);
     k_sel_finalize<<<(unsigned)((F + 3) / 4), 256, 0, s>>>(
@@ -1171,14 +1321,14 @@ void launch_select_pruned(ivx_ctx* ctx, const float* X, int64_t F, int* post_idx
   Presel& P = *ctx->presel;
   {
     ProfScope ps(ctx, PK_SEL_MLP, s);
-    k_diag_prepare<<<(ctx->Cpad + 255) / 256, 256, 0, s>>>(ctx->w, ctx->mu, ctx->cov, ctx->shift,
+    k_diag_prepare<<<(ctx->Cpad + 3) / 4, 256, 0, s>>>(ctx->w, ctx->mu, ctx->cov, ctx->shift,
                                                            ctx->C, ctx->Cpad, ctx->D, P.Kd8, P.Wd);
     const int km = l3_km(P.k);
     const unsigned nb = (unsigned)((F + 127) / 128);
-    const size_t lds = diag_lds_bytes(ctx->D, P.Kd8, km);
+    const size_t lds = diag_lds_bytes(ctx->D, km);
 #define IVX_DIAG(KMV)                                                                          \
-  k_diag_topk<KMV><<<nb, 256, lds, s>>>(X, F, ctx->D, ctx->shift, P.Wd, ctx->C, ctx->Cpad,      \
-                                        P.Kd8, P.pairs, P.k, P.prop)
+  k_diag_topk<KMV><<<nb, 256, lds, s>>>(X, F, ctx->D, ctx->shift, P.Wd, ctx->Cpad, P.Kd8, P.k,  \
+                                        P.prop)
     if (km == 8)
       IVX_DIAG(8);
     else if (km == 20)
@@ -1194,8 +1344,7 @@ void launch_select_pruned(ivx_ctx* ctx, const float* X, int64_t F, int* post_idx
   launch_hist_scan(nb, ctx->C, P.hist, P.coff, s);
   k_sel_scatter<<<nb, 256, ldsc, s>>>(F, fpb, P.k, ctx->C, P.prop, nullptr, P.hist, P.coff, P.ent);
   const int64_t cap = F * P.k;
-  k_sel_score<<<(unsigned)((cap + 255) / 256), 256, 0, s>>>(
-      X, ctx->D, P.k, P.coff, ctx->C, P.ent, cap, ctx->mu, ctx->linv32r, ctx->cst, P.score);
+  launch_sel_score(ctx, X, P.k, P.coff, P.ent, cap, P.score, s);
   exact_kept(ctx, X, F, P.k, P.prop, nullptr, P.score, P.margin, P.thr, P.hist, P.coff, P.ent,
              P.lscore, s);
   k_sel_finalize<<<(unsigned)((F + 3) / 4), 256, 0, s>>>(

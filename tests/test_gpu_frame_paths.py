@@ -114,3 +114,32 @@ def test_small_batch_route_equals_dense_route(C, D, F, prec):
     b = _lists(ctx, X, prec)
     for p, q in zip(a, b):
         np.testing.assert_array_equal(p, q)
+
+
+@pytest.mark.parametrize("C,D,F,k", [(1, 1, 1, 1), (64, 20, 33, 21), (40, 5, 127, 8),
+                                     (130, 33, 129, 9), (257, 63, 130, 20), (300, 60, 257, 32)])
+def test_pruned_alignment_at_list_and_tile_edges(C, D, F, k):
+    """Frame log-likelihoods over the k best components of the diagonal UBM:
+    FP64 of the kept proposals, so 1e-6 as for the larger workloads, wherever
+    the k-th and the next diagonal score differ by more than the FP32 sums may
+    (2 x 128 roundings of the terms' magnitude on either side)."""
+    from paper_1906_08556_amd import ivx
+    wl = synth.make(2, C=C, D=D, R=4, U=1, lengths=f"uniform:{F}:{F}")
+    ctx = make_ctx(wl)
+    ctx.pruned_set(k, 0.025)
+    ll = torch.empty(F, dtype=torch.float64, device="cuda")
+    ctx.ubm_posteriors(dev(wl.X), frame_ll=ll, sel=ivx.IVX_SEL_PRUNED)
+    ctx.sync_status()
+    lld = oracle.diag_frame_loglik(wl.X, wl.w, wl.mu, wl.cov)
+    order = oracle.preselect(lld, min(k + 1, C))
+    _, lse = oracle.pruned_posteriors(wl.X, wl.w, wl.mu, wl.cov, order[:, :k], 0.025)
+    clear = np.ones(F, bool)
+    if k < C:
+        var = np.stack([np.diag(c) for c in wl.cov])
+        x = np.abs(wl.X.astype(np.float64) - (wl.w[:, None] * wl.mu).sum(0))
+        m = np.abs(wl.mu - (wl.w[:, None] * wl.mu).sum(0))
+        mag = x @ (m / var).T + (x ** 2) @ (0.5 / var).T + (0.5 * m ** 2 / var).sum(1) + 4 * D
+        gap = np.take_along_axis(lld, order[:, k - 1:k], 1) - np.take_along_axis(lld, order[:, k:], 1)
+        clear = gap[:, 0] > 2 * 2 * 128 * 2.0 ** -24 * mag.max(1)
+    assert clear.mean() > 0.5
+    assert np.abs(ll.cpu().numpy() - lse)[clear].max() <= 1e-6
