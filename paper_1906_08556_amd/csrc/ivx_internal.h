@@ -194,6 +194,8 @@ struct ivx_ctx {
   int* bmax = nullptr;        // [1] largest magnitude of both (float bits)
   _Float16* Wf = nullptr;     // [Cpad/2][2][4][64][8] scaled W_c in MFMA fragment order
   float2* cb = nullptr;       // [Cpad] scaled constants of the bound's test
+  uint16_t* sums16 = nullptr;  // [sweep_frames][Cpad] 16-row sums between the sweeps
+  int64_t sweep_frames = 0;    // frames per pass of the sweeps
   float* lquad = nullptr;     // [C][16][64][4] L_c^{-1} in FP32, four columns per row
   double* cst = nullptr;      // [C] log w_c - D/2 log 2pi - sum_i log L_c[i,i]
   uint16_t* pairs = nullptr;  // [Kpad] expanded-feature index pairs (a | b << 8)
@@ -341,6 +343,9 @@ void launch_scores_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hip
 
 // ---- k_bound.hip
 bool bound_supported(int C, int D);
+// frames the sweeps take at a time: 2 GB of sums (524288 frames at C = 2048; the
+// device works on 262144), at least one block of frames per wave
+int64_t bound_sweep_frames(int Cpad, int64_t maxF);
 bool bound_set_attributes(const ivx_ctx* ctx);
 void launch_bound_prepare(ivx_ctx* ctx, bool cov_changed, hipStream_t s);
 // Candidate lists as the dense kernel leaves them; the frames that only the

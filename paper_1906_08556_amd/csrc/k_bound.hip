@@ -342,27 +342,45 @@ __device__ inline void dma16(const uint4* src, uint4* dst) {
 }
 __device__ inline void dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// Between the sweeps the 16-row sums of all pairs are kept, so that sweep 2 need
+// not form them again: in nats, as FP16 cut towards zero (below 65504), which
+// only lowers them: the bound stays a bound.  A lane's values of the CH pairs
+// of a stage are 8 bytes, [tile][stage][block][thread].  (8 bits would not do:
+// thresholds of 2000 nats are usual, and the cut must stay at a few nats.)
+static_assert(CH == 4, "four values per 8 bytes");
+typedef __fp16 cut2 __attribute__((ext_vector_type(2)));
+typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
+__device__ inline uint32_t cut_pair(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(a, b));
+}
+__device__ inline float cut_value(uint32_t w, int half) {
+  return (float)__builtin_bit_cast(cut2, w)[half];
+}
+
 // Sweep 1: the component with the largest bound (16 rows) of every frame.
 template <int FB>
 __global__ void __launch_bounds__(64 * BW, 4)
-k_bound_best(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int64_t F,
-             const _Float16* __restrict__ Wf, const float2* __restrict__ cb, int npair,
-             int* __restrict__ best, const int* __restrict__ Fdev) {
+k_bound_best(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int64_t f0, int64_t F,
+             const _Float16* __restrict__ Wf, const float2* __restrict__ cb,
+             const int* __restrict__ maxbits, int npair, int* __restrict__ best,
+             uint2v* __restrict__ sums, const int* __restrict__ Fdev) {
   __shared__ __attribute__((aligned(16))) uint4 st[2][CH * 256];
   __shared__ float sc[2][2 * CH];
   if (Fdev && (int64_t)Fdev[0] < F) F = Fdev[0];
   constexpr int FT = 32 * BW * FB;
-  const int64_t ntile = (F + FT - 1) / FT;
+  const int64_t ntile = (F - f0 + FT - 1) / FT;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5, l32 = lane & 31;
   const uint4* W4 = reinterpret_cast<const uint4*>(Wf) + (size_t)(tid >> 8) * 512 + (tid & 255);
   const int nch = npair / CH;
+  const float S = bound_scale(maxbits);
   for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
-    const int64_t fw = tile * FT + wave * 32 * FB;
+    const int64_t fw = f0 + tile * FT + wave * 32 * FB;
     half8 xf[FB][4];
-    float t2[FB], bv[FB];
+    float t2[FB], rn[FB], bv[FB];
     int bc[FB];
+    float v[FB][CH];
 #pragma unroll
     for (int fb = 0; fb < FB; ++fb) {
       const int64_t g = min(fw + 32 * fb + l32, F - 1);
@@ -370,6 +388,7 @@ k_bound_best(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
       for (int ks = 0; ks < 4; ++ks)
         xf[fb][ks] = *reinterpret_cast<const half8*>(xh + g * BK + 16 * ks + 8 * h);
       t2[fb] = tg[g].x;
+      rn[fb] = 0.5f / (S * S * t2[fb]);
       bv[fb] = INFINITY;
       bc[fb] = -1;
     }
@@ -379,6 +398,13 @@ k_bound_best(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
       dma16(W4 + (size_t)ch * CH * 512 + 1024, &st[b][512 + wave * 64]);
       if (tid < 2 * CH) sc[b][tid] = cb[2 * CH * ch + tid].x;
     };
+    uint2v* ct = sums + (size_t)tile * nch * FB * (64 * BW) + tid;
+    uint2v w[FB];
+    auto put = [&](int ch) {
+#pragma unroll
+      for (int fb = 0; fb < FB; ++fb)
+        __builtin_nontemporal_store(w[fb], ct + (size_t)(ch * FB + fb) * (64 * BW));
+    };
     __syncthreads();  // the previous tile's stage is consumed
     stage(0, 0);
     dma_wait();
@@ -387,7 +413,8 @@ k_bound_best(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
     for (int ch = 0; ch < nch; ++ch) {
       const int b = ch & 1;
       if (ch + 1 < nch) stage(ch + 1, b ^ 1);  // last read before the previous barrier
-#pragma unroll 1
+      if (ch > 0) put(ch - 1);                 // complete by the wait below
+#pragma unroll
       for (int i = 0; i < CH; ++i) {
         half8 a[4];
 #pragma unroll
@@ -406,16 +433,22 @@ k_bound_best(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
         const int c = 2 * (ch * CH + i) + h;
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb) {
-          float q = -u * t2[fb];
+          float sq = acc[fb][0] * acc[fb][0];
 #pragma unroll
-          for (int r = 0; r < 16; ++r) q = fmaf(acc[fb][r], acc[fb][r], q);
+          for (int r = 1; r < 16; ++r) sq = fmaf(acc[fb][r], acc[fb][r], sq);
+          const float q = fmaf(-u, t2[fb], sq);
           bc[fb] = q < bv[fb] ? c : bc[fb];
           bv[fb] = fminf(q, bv[fb]);
+          v[fb][i] = sq * rn[fb];
         }
       }
+#pragma unroll
+      for (int fb = 0; fb < FB; ++fb)
+        w[fb] = uint2v{cut_pair(v[fb][0], v[fb][1]), cut_pair(v[fb][2], v[fb][3])};
       dma_wait();
       __syncthreads();
     }
+    put(nch - 1);
 #pragma unroll
     for (int fb = 0; fb < FB; ++fb) {
       const float ov = __shfl_xor(bv[fb], 32);
@@ -428,30 +461,31 @@ k_bound_best(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
 }
 
 // Sweep 2: the components whose bound reaches the threshold M - margin, M the
-// exact score of the component of sweep 1 (in cM, best in flag).  The second
-// 16 rows are formed where any lane of the wave passes on the first 16.
+// exact score of the component of sweep 1 (in cM, best in flag).  The first 16
+// rows come from sweep 1 (the same tiles); the second 16 rows are
+// formed where any lane of the wave passes on the first 16.
 // Lists: surv [F][2][32] component ids, counts (or -1) over flag.
 template <int FB>
 __global__ void __launch_bounds__(64 * BW, 4)
-k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int64_t F,
+k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int64_t f0, int64_t F,
              const _Float16* __restrict__ Wf, const float2* __restrict__ cb,
              const int* __restrict__ maxbits, int npair, float margin,
-             const float* __restrict__ Mf, uint16_t* __restrict__ surv, int* __restrict__ flag,
-             const int* __restrict__ Fdev) {
-  __shared__ __attribute__((aligned(16))) uint4 st[2][CH * 512];
+             const float* __restrict__ Mf, const uint2v* __restrict__ sums,
+             uint16_t* __restrict__ surv, int* __restrict__ flag, const int* __restrict__ Fdev) {
+  __shared__ __attribute__((aligned(16))) uint4 st[2][CH * 256];
   __shared__ float2 sc[2][2 * CH];
   if (Fdev && (int64_t)Fdev[0] < F) F = Fdev[0];
   constexpr int FT = 32 * BW * FB;
-  const int64_t ntile = (F + FT - 1) / FT;
+  const int64_t ntile = (F - f0 + FT - 1) / FT;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5, l32 = lane & 31;
-  const uint4* W4 = reinterpret_cast<const uint4*>(Wf) + tid;
+  const uint4* W4 = reinterpret_cast<const uint4*>(Wf) + (size_t)(tid >> 8) * 512 + 256 + (tid & 255);
   const int nch = npair / CH;
   for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
-    const int64_t fw = tile * FT + wave * 32 * FB;
+    const int64_t fw = f0 + tile * FT + wave * 32 * FB;
     half8 xf[FB][4];
-    float k1[FB], k2[FB], k3[FB];
+    float k1[FB], k2[FB], k3[FB], rn[FB];  // in nats: the test is k1 u + k2 e - k3 >= v
     int cnt[FB];
 #pragma unroll
     for (int fb = 0; fb < FB; ++fb) {
@@ -473,73 +507,72 @@ k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
         eta = fminf(fmaxf(sqrtf(cv.y / T) * q.y, 0.0009765625f), 8.0f);
         if (!(eta > 0.0f)) eta = 1.0f;
       }
-      k1[fb] = (1.0f + eta) * q.x;
-      k2[fb] = (1.0f + 1.0f / eta) * q.y * q.y;
-      k3[fb] = k1[fb] * S2x2 * thr;
-      good = good && isfinite(k3[fb]) && isfinite(k2[fb]);
+      rn[fb] = 1.0f / (S2x2 * q.x);
+      k1[fb] = (1.0f + eta) / S2x2;
+      k2[fb] = (1.0f + 1.0f / eta) * q.y * q.y * rn[fb];
+      k3[fb] = (1.0f + eta) * thr;
+      good = good && isfinite(k1[fb]) && isfinite(k2[fb]) && isfinite(k3[fb]) && isfinite(rn[fb]);
       if (!good) {
         k1[fb] = k2[fb] = 0.0f;
         k3[fb] = INFINITY;
       }
       cnt[fb] = good ? 0 : SL + 1;
     }
+    // stage ch in buffer b: the second 16 rows of CH pairs and their constants
     auto stage = [&](int ch, int b) {
-      const uint4* p = W4 + (size_t)ch * CH * 512;
-      uint4* d = &st[b][wave * 64];
-      dma16(p, d);
-      dma16(p + 512, d + 512);
-      dma16(p + 1024, d + 1024);
-      dma16(p + 1536, d + 1536);
+      dma16(W4 + (size_t)ch * CH * 512, &st[b][wave * 64]);
+      dma16(W4 + (size_t)ch * CH * 512 + 1024, &st[b][512 + wave * 64]);
       if (tid < 2 * CH) sc[b][tid] = cb[2 * CH * ch + tid];
+    };
+    const uint2v* ct = sums + (size_t)tile * nch * FB * (64 * BW) + tid;
+    uint2v w[FB], next[FB];
+    auto get = [&](int ch) {
+#pragma unroll
+      for (int fb = 0; fb < FB; ++fb)
+        next[fb] = __builtin_nontemporal_load(ct + (size_t)(ch * FB + fb) * (64 * BW));
     };
     __syncthreads();  // the previous tile's stage is consumed
     stage(0, 0);
+    get(0);
     dma_wait();
     __syncthreads();
 #pragma unroll 1
     for (int ch = 0; ch < nch; ++ch) {
       const int b = ch & 1;
-      if (ch + 1 < nch) stage(ch + 1, b ^ 1);  // last read before the previous barrier
-#pragma unroll 1
+#pragma unroll
+      for (int fb = 0; fb < FB; ++fb) w[fb] = next[fb];
+      if (ch + 1 < nch) {
+        stage(ch + 1, b ^ 1);  // last read before the previous barrier
+        get(ch + 1);
+      }
+#pragma unroll
       for (int i = 0; i < CH; ++i) {
+        const float2 cv = sc[b][2 * i + h];
+        float t[FB], v[FB];
+        bool pass[FB], any = false;
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb) {
+          t[fb] = fmaf(k1[fb], cv.x, fmaf(k2[fb], cv.y, -k3[fb]));
+          v[fb] = cut_value(w[fb][i >> 1], i & 1);
+          pass[fb] = v[fb] <= t[fb];
+          any = any || pass[fb];
+        }
+        if (__ballot(any) == 0) continue;
         half8 a[4];
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
-          a[ks] = *reinterpret_cast<const half8*>(&st[b][i * 512 + ks * 64 + lane]);
-        const float2 cv = sc[b][2 * i + h];
-        floatx16 acc[FB];
-#pragma unroll
-        for (int fb = 0; fb < FB; ++fb)
-          acc[fb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0], xf[fb][0], floatx16{0}, 0, 0, 0);
-#pragma unroll
-        for (int ks = 1; ks < 4; ++ks)
-#pragma unroll
-          for (int fb = 0; fb < FB; ++fb)
-            acc[fb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ks], xf[fb][ks], acc[fb], 0, 0, 0);
-        float q[FB];
-        bool any = false;
+          a[ks] = *reinterpret_cast<const half8*>(&st[b][i * 256 + ks * 64 + lane]);
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb) {
-          q[fb] = fmaf(-k1[fb], cv.x, fmaf(-k2[fb], cv.y, k3[fb]));
-#pragma unroll
-          for (int r = 0; r < 16; ++r) q[fb] = fmaf(acc[fb][r], acc[fb][r], q[fb]);
-          any = any || q[fb] <= 0.0f;
-        }
-        if (__ballot(any) == 0) continue;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-          a[ks] = *reinterpret_cast<const half8*>(&st[b][i * 512 + 256 + ks * 64 + lane]);
-#pragma unroll
-        for (int fb = 0; fb < FB; ++fb) {
-          if (__ballot(q[fb] <= 0.0f) == 0) continue;
+          if (__ballot(pass[fb]) == 0) continue;
           floatx16 ac = floatx16{0};
 #pragma unroll
           for (int ks = 0; ks < 4; ++ks)
             ac = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ks], xf[fb][ks], ac, 0, 0, 0);
-          float qq = q[fb];
+          float sq = ac[0] * ac[0];
 #pragma unroll
-          for (int r = 0; r < 16; ++r) qq = fmaf(ac[r], ac[r], qq);
-          if (qq <= 0.0f) {
+          for (int r = 1; r < 16; ++r) sq = fmaf(ac[r], ac[r], sq);
+          if (pass[fb] && fmaf(sq, rn[fb], v[fb]) <= t[fb]) {
             const int64_t g = fw + 32 * fb + l32;
             if (cnt[fb] < SL) surv[g * 64 + h * SL + cnt[fb]] = (uint16_t)(2 * (ch * CH + i) + h);
             ++cnt[fb];
@@ -561,13 +594,13 @@ k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
 // --------------------------------------------------------- pairs by component
 // Sweep 1: one pair (frame, best) per frame.
 __global__ void __launch_bounds__(256)
-k_best_hist(int64_t F, int fpb, int C, const int* __restrict__ best, const int* __restrict__ Fdev,
+k_best_hist(int64_t f0, int64_t F, int fpb, int C, const int* __restrict__ best, const int* __restrict__ Fdev,
             int* __restrict__ hist) {
   extern __shared__ int hl[];
   if (Fdev && (int64_t)Fdev[0] < F) F = Fdev[0];
   for (int c = threadIdx.x; c < C; c += 256) hl[c] = 0;
   __syncthreads();
-  const int64_t g0 = (int64_t)blockIdx.x * fpb, g1 = min(F, g0 + fpb);
+  const int64_t g0 = f0 + (int64_t)blockIdx.x * fpb, g1 = min(F, g0 + fpb);
   for (int64_t g = g0 + threadIdx.x; g < g1; g += 256) {
     const int c = best[g];
     if (c >= 0) atomicAdd(&hl[c], 1);
@@ -577,14 +610,14 @@ k_best_hist(int64_t F, int fpb, int C, const int* __restrict__ best, const int* 
 }
 
 __global__ void __launch_bounds__(256)
-k_best_scatter(int64_t F, int fpb, int C, const int* __restrict__ best,
+k_best_scatter(int64_t f0, int64_t F, int fpb, int C, const int* __restrict__ best,
                const int* __restrict__ Fdev, const int* __restrict__ base,
                const int* __restrict__ coff, int2* __restrict__ ent) {
   extern __shared__ int cur[];
   if (Fdev && (int64_t)Fdev[0] < F) F = Fdev[0];
   for (int c = threadIdx.x; c < C; c += 256) cur[c] = coff[c] + base[(size_t)blockIdx.x * C + c];
   __syncthreads();
-  const int64_t g0 = (int64_t)blockIdx.x * fpb, g1 = min(F, g0 + fpb);
+  const int64_t g0 = f0 + (int64_t)blockIdx.x * fpb, g1 = min(F, g0 + fpb);
   for (int64_t g = g0 + threadIdx.x; g < g1; g += 256) {
     const int c = best[g];
     if (c >= 0) ent[atomicAdd(&cur[c], 1)] = make_int2((int)g, c);
@@ -966,6 +999,11 @@ size_t dirs_lds(int D) { return sizeof(double) * ((size_t)D * D + 2 * (size_t)D 
 // The bound needs D + 2 <= 64 columns and at least 32 dimensions for its rows,
 // 16-bit component ids, and enough components that sweeping them twice on
 // FP16 with 16 rows is cheaper than once in FP32 with (D + 1)(D + 2) / 2.
+int64_t bound_sweep_frames(int Cpad, int64_t maxF) {
+  const int64_t n = std::max<int64_t>(int64_t(1) << 17, (int64_t(1) << 30) / Cpad / 512 * 512);
+  return std::min<int64_t>(n, (maxF + 511) / 512 * 512);
+}
+
 bool bound_supported(int C, int D) { return D >= BR && D + 2 <= BK && C >= 512 && C <= 65536; }
 
 bool bound_set_attributes(const ivx_ctx* ctx) {
@@ -1018,27 +1056,39 @@ void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipS
   const unsigned nb = (unsigned)((F + fpb - 1) / fpb);
   const size_t ldsc = sizeof(int) * ctx->C;
   const unsigned n16 = (unsigned)((F + 15) / 16);
-  // frames per tile: 256 FB; two blocks per wave halve the LDS reads per MFMA,
-  // one fills the device with half the frames
-  const int64_t slots = 2 * (int64_t)ctx->ncu;
-  const int64_t t2 = (F + 511) / 512, t1 = (F + 255) / 256;
-  const bool two = 2.0 * (double)((t2 + slots - 1) / slots) <= 1.3 * (double)((t1 + slots - 1) / slots);
-  const unsigned nblk = (unsigned)std::min<int64_t>(two ? t2 : t1, slots);
   const unsigned nq = (unsigned)std::min<int64_t>((F + 31) / 32, 2 * (int64_t)ctx->ncu);
   const unsigned ne = (unsigned)std::min<int64_t>((F + 63) / 64, 8 * (int64_t)ctx->ncu);
   ProfScope ps(ctx, PK_FRAME_SELECT, s);
   k_bound_frames<<<n16, 256, 0, s>>>(X, F, ctx->D, ctx->shift, Fdev, xh, tg);
-  (two ? k_bound_best<2> : k_bound_best<1>)<<<nblk, 64 * BW, 0, s>>>(
-      xh, tg, F, ctx->Wf, ctx->cb, ctx->Cpad / 2, ctx->cflag, Fdev);
-  k_best_hist<<<nb, 256, ldsc, s>>>(F, fpb, ctx->C, ctx->cflag, Fdev, ctx->hist);
-  launch_hist_scan((int)nb, ctx->C, ctx->hist, ctx->coff, s);
-  k_best_scatter<<<nb, 256, ldsc, s>>>(F, fpb, ctx->C, ctx->cflag, Fdev, ctx->hist, ctx->coff, ent1);
   const bool v4 = ctx->D % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
-  (v4 ? k_bound_quad<true> : k_bound_quad<false>)<<<nq, 256, 0, s>>>(
-      X, ctx->D, ctx->coff, ctx->C, ent1, F, ctx->mu, ctx->lquad, ctx->cst, nullptr, ctx->cM);
-  (two ? k_bound_list<2> : k_bound_list<1>)<<<nblk, 64 * BW, 0, s>>>(
-      xh, tg, F, ctx->Wf, ctx->cb, ctx->bmax, ctx->Cpad / 2, margin + err - 3.0f, ctx->cM, surv,
-      ctx->cflag, Fdev);
+  // the sweeps over as many frames as their sums have room for, in equal parts
+  uint2v* sums = reinterpret_cast<uint2v*>(ctx->sums16);
+  const int64_t parts = (F + ctx->sweep_frames - 1) / ctx->sweep_frames;
+  const int64_t step = ((F + parts - 1) / parts + 511) / 512 * 512;
+  for (int64_t f0 = 0; f0 < F; f0 += step) {
+    const int64_t f1 = std::min(F, f0 + step), n = f1 - f0;
+    // frames per tile: 256 FB; two blocks per wave halve the LDS reads per MFMA,
+    // one fills the device with half the frames
+    const int64_t slots = 2 * (int64_t)ctx->ncu;
+    const int64_t t2 = (n + 511) / 512, t1 = (n + 255) / 256;
+    const bool two =
+        2.0 * (double)((t2 + slots - 1) / slots) <= 1.3 * (double)((t1 + slots - 1) / slots);
+    const unsigned nblk = (unsigned)std::min<int64_t>(two ? t2 : t1, slots);
+    const int fpp = hist_frames(n, ctx->nhist);
+    const unsigned np = (unsigned)((n + fpp - 1) / fpp);
+    (two ? k_bound_best<2> : k_bound_best<1>)<<<nblk, 64 * BW, 0, s>>>(
+        xh, tg, f0, f1, ctx->Wf, ctx->cb, ctx->bmax, ctx->Cpad / 2, ctx->cflag, sums, Fdev);
+    k_best_hist<<<np, 256, ldsc, s>>>(f0, f1, fpp, ctx->C, ctx->cflag, Fdev, ctx->hist);
+    launch_hist_scan((int)np, ctx->C, ctx->hist, ctx->coff, s);
+    k_best_scatter<<<np, 256, ldsc, s>>>(f0, f1, fpp, ctx->C, ctx->cflag, Fdev, ctx->hist,
+                                         ctx->coff, ent1);
+    const unsigned nq1 = (unsigned)std::min<int64_t>((n + 31) / 32, 2 * (int64_t)ctx->ncu);
+    (v4 ? k_bound_quad<true> : k_bound_quad<false>)<<<nq1, 256, 0, s>>>(
+        X, ctx->D, ctx->coff, ctx->C, ent1, n, ctx->mu, ctx->lquad, ctx->cst, nullptr, ctx->cM);
+    (two ? k_bound_list<2> : k_bound_list<1>)<<<nblk, 64 * BW, 0, s>>>(
+        xh, tg, f0, f1, ctx->Wf, ctx->cb, ctx->bmax, ctx->Cpad / 2, margin + err - 3.0f, ctx->cM,
+        sums, surv, ctx->cflag, Fdev);
+  }
   k_bound_hist<<<nb, 256, ldsc, s>>>(F, fpb, ctx->C, surv, ctx->cflag, Fdev, ctx->hist, cnts);
   launch_hist_scan((int)nb, ctx->C, ctx->hist, ctx->coff, s);
   k_bound_scatter<<<nb, 256, ldsc, s>>>(F, fpb, ctx->C, ctx->cand, ctx->cflag, Fdev, ctx->hist,
