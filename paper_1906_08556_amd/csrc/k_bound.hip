@@ -13,15 +13,17 @@
 //   smallest eigenvalues of Sigma_c carry most of the distance.
 //
 // W_c x' (x' = x - shift) runs on v_mfma_f32_32x32x16_f16; the rounding of
-// both operands to FP16 is covered by a bound on its norm (see k_bound), so a
+// both operands to FP16 is covered by a bound on its norm (see below), so a
 // component is dropped only when its score is certainly more than the margin
 // below the frame's best.  The steps, per batch:
 //
-//   k_bound         sweep 1 over all components finds the frame's best bound
-//                   (16 rows), whose component is scored exactly (FP32 L^-1):
-//                   M, a lower limit of the frame's maximum.  Sweep 2 lists the
-//                   components whose bound (16 rows, then 32 where any lane of
-//                   the wave needs them) reaches M - margin.
+//   k_bound_best    sweep 1 over all components finds the frame's best bound
+//                   (16 rows) and keeps the sums of all; the best component is
+//                   scored exactly (FP32 L^-1): M, a lower limit of the frame's
+//                   maximum
+//   k_bound_list    sweep 2 lists the components whose bound (the kept 16 rows,
+//                   then 32 where any lane of the wave needs them) reaches
+//                   M - margin
 //   k_bound_hist / scan / k_bound_scatter
 //                   the listed pairs bucketed by component
 //   k_bound_quad    FP32 score of every pair through L_c^-1, per-frame maximum
@@ -51,7 +53,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 constexpr int BR = 32;            // bound rows per component (two blocks of 16)
 constexpr int BK = 64;            // features: D, mean (high, low), zero padding
 constexpr int BW = 8;             // waves per workgroup of k_bound
-constexpr int CH = 4;             // row blocks (component pairs) per LDS stage
+constexpr int CH = 4;             // row blocks (component pairs) per LDS stage, sweep 1
+constexpr int CL = 8;             // and sweep 2
 constexpr int SL = 32;            // listed components per lane-half and frame
 constexpr int kReplay = 1 << 16;    // flag bits above the candidate count
 constexpr int kFallback = 1 << 20;
@@ -326,12 +329,16 @@ k_bound_frames(const float* __restrict__ X, int64_t F, int D, const float* __res
 
 // Both sweeps: one persistent workgroup of 8 waves per 256 FB frames, FB blocks
 // of 32 frames per wave (lane l: frame l % 32 of each block, component parity
-// l / 32).  Bound by the matrix cores and the vector units alike: per 32 x 32
-// block 4 MFMAs (128 cycles) and 19 vector instructions (76 cycles), which
-// overlap between the four waves of a SIMD.  The FP16 operand of a pair of
-// components (4 KB per 16 rows) is staged through LDS in fragment order and
-// serves the FB frame blocks of all waves; at one block per wave the LDS reads
-// alone would take as long as the MFMAs.
+// l / 32).  Sweep 1 is bound by the matrix cores (per 32 x 32 block 4 MFMAs, 128
+// cycles, and 21 vector instructions, 84 cycles, which overlap between the four
+// waves of a SIMD) and by power: 4 M frames at C = 2048 take 15.1 ms at 1.64 GHz,
+// 68 % of the cycles in MFMAs.  The FP16 operand of a pair of components (4 KB
+// per 16 rows) is staged through LDS in fragment order and serves the FB frame
+// blocks of all waves; at one block per wave the LDS reads alone would take as
+// long as the MFMAs.  Sweep 2 reads the sums (16 GB) and forms the second 16
+// rows of 43 % of the blocks: 11.1 ms with 8 pairs per stage, 12.7 with 4 (its
+// stages are short, the loads of the next must be complete at their end), 22 ms
+// when it formed the first 16 rows again.
 
 // 16 bytes per lane from device memory straight into LDS: lane l's at dst + 16 l
 // (dst wave-uniform).  Complete after dma_wait() and a barrier.
@@ -472,8 +479,8 @@ k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
              const int* __restrict__ maxbits, int npair, float margin,
              const float* __restrict__ Mf, const uint2v* __restrict__ sums,
              uint16_t* __restrict__ surv, int* __restrict__ flag, const int* __restrict__ Fdev) {
-  __shared__ __attribute__((aligned(16))) uint4 st[2][CH * 256];
-  __shared__ float2 sc[2][2 * CH];
+  __shared__ __attribute__((aligned(16))) uint4 st[2][CL * 256];
+  __shared__ float2 sc[2][2 * CL];
   if (Fdev && (int64_t)Fdev[0] < F) F = Fdev[0];
   constexpr int FT = 32 * BW * FB;
   const int64_t ntile = (F - f0 + FT - 1) / FT;
@@ -481,7 +488,7 @@ k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5, l32 = lane & 31;
   const uint4* W4 = reinterpret_cast<const uint4*>(Wf) + (size_t)(tid >> 8) * 512 + 256 + (tid & 255);
-  const int nch = npair / CH;
+  const int nch = npair / CL;  // Cpad is a multiple of 256
   for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
     const int64_t fw = f0 + tile * FT + wave * 32 * FB;
     half8 xf[FB][4];
@@ -518,42 +525,42 @@ k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
       }
       cnt[fb] = good ? 0 : SL + 1;
     }
-    // stage ch in buffer b: the second 16 rows of CH pairs and their constants
+    // stage ch in buffer b: the second 16 rows of CL pairs and their constants
     auto stage = [&](int ch, int b) {
-      dma16(W4 + (size_t)ch * CH * 512, &st[b][wave * 64]);
-      dma16(W4 + (size_t)ch * CH * 512 + 1024, &st[b][512 + wave * 64]);
-      if (tid < 2 * CH) sc[b][tid] = cb[2 * CH * ch + tid];
+#pragma unroll
+      for (int j = 0; j < CL / 2; ++j)
+        dma16(W4 + (size_t)ch * CL * 512 + 1024 * j, &st[b][512 * j + wave * 64]);
+      if (tid < 2 * CL) sc[b][tid] = cb[2 * CL * ch + tid];
     };
-    const uint2v* ct = sums + (size_t)tile * nch * FB * (64 * BW) + tid;
-    uint2v w[FB], next[FB];
-    auto get = [&](int ch) {
+    const uint2v* ct = sums + (size_t)tile * nch * 2 * FB * (64 * BW) + tid;
+    // half a stage's sums, loaded half a stage ahead
+    uint2v w[2][FB];
+    auto get = [&](int ch, int j) {
 #pragma unroll
       for (int fb = 0; fb < FB; ++fb)
-        next[fb] = __builtin_nontemporal_load(ct + (size_t)(ch * FB + fb) * (64 * BW));
+        w[j][fb] = __builtin_nontemporal_load(ct + (size_t)((2 * ch + j) * FB + fb) * (64 * BW));
     };
+    static_assert(CL == 2 * CH, "two halves");
     __syncthreads();  // the previous tile's stage is consumed
     stage(0, 0);
-    get(0);
+    get(0, 0);
     dma_wait();
     __syncthreads();
 #pragma unroll 1
     for (int ch = 0; ch < nch; ++ch) {
       const int b = ch & 1;
+      if (ch + 1 < nch) stage(ch + 1, b ^ 1);  // last read before the previous barrier
+      get(ch, 1);
 #pragma unroll
-      for (int fb = 0; fb < FB; ++fb) w[fb] = next[fb];
-      if (ch + 1 < nch) {
-        stage(ch + 1, b ^ 1);  // last read before the previous barrier
-        get(ch + 1);
-      }
-#pragma unroll
-      for (int i = 0; i < CH; ++i) {
+      for (int i = 0; i < CL; ++i) {
+        if (i == CH) get(min(ch + 1, nch - 1), 0);
         const float2 cv = sc[b][2 * i + h];
         float t[FB], v[FB];
         bool pass[FB], any = false;
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb) {
           t[fb] = fmaf(k1[fb], cv.x, fmaf(k2[fb], cv.y, -k3[fb]));
-          v[fb] = cut_value(w[fb][i >> 1], i & 1);
+          v[fb] = cut_value(w[i / CH][fb][i % CH >> 1], i & 1);
           pass[fb] = v[fb] <= t[fb];
           any = any || pass[fb];
         }
@@ -574,7 +581,7 @@ k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
           for (int r = 1; r < 16; ++r) sq = fmaf(ac[r], ac[r], sq);
           if (pass[fb] && fmaf(sq, rn[fb], v[fb]) <= t[fb]) {
             const int64_t g = fw + 32 * fb + l32;
-            if (cnt[fb] < SL) surv[g * 64 + h * SL + cnt[fb]] = (uint16_t)(2 * (ch * CH + i) + h);
+            if (cnt[fb] < SL) surv[g * 64 + h * SL + cnt[fb]] = (uint16_t)(2 * (ch * CL + i) + h);
             ++cnt[fb];
           }
         }
