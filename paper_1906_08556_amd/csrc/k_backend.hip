@@ -301,17 +301,16 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 // The same with a whitening matrix, 16 rows per workgroup: W (x - mean) on FP64
 // MFMA (16 x 16 x 4), the centred rows in LDS, every wave the output columns
-// 16 (wave + 4 t).  A lane reads four consecutive entries of a row of W per 16
-// columns (contraction index 4 (lane / 16) + e), so the 16 rows of a tile are
-// read in whole 128-byte pieces; a lane per output read a column of strided
-// entries for every row.  1200 rows of 400: 113 us (bound by one workgroup's chain
-// of MFMAs, 75 workgroups), a lane per output 284 us.
+// 16 (wave + 4 t).  The matrix cores add the products one by one in the order of
+// the columns, and the squares are added as the wave per row of k_lnorm would,
+// so a row is the one that a lane per output forms.  1200 rows of 400: 113 us
+// (bound by one workgroup's chain of MFMAs, 75 workgroups), a lane per output
+// 284 us (it read a column of strided entries of W for every row).
 constexpr int LN_T = LN_MAX / 64;  // output tiles per wave
 __global__ void __launch_bounds__(256)
 k_lnorm_white(const float* __restrict__ X, int64_t n, int dim, const double* __restrict__ mean,
               const double* __restrict__ W, float* __restrict__ Y) {
-  extern __shared__ double t[];  // [16][ld], zero beyond dim
-  __shared__ double ssw[4][16];
+  extern __shared__ double t[];  // [16][ld], zero beyond dim; then the products
   const int ld = (dim + 15) / 16 * 16 + 2;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l16 = lane & 15, q16 = lane >> 4;
   const int64_t r0 = (int64_t)blockIdx.x * 16;
@@ -322,7 +321,6 @@ k_lnorm_white(const float* __restrict__ X, int64_t n, int dim, const double* __r
   __syncthreads();
   const int nt = (dim + 15) / 16;
   doublex4 acc[LN_T];
-  double ss[4] = {0.0, 0.0, 0.0, 0.0};  // rows 4 r + q16
 #pragma unroll
   for (int u = 0; u < LN_T; ++u) {
     const int tile = w + 4 * u;
@@ -331,34 +329,32 @@ k_lnorm_white(const float* __restrict__ X, int64_t n, int dim, const double* __r
     const int col = 16 * tile + l16;
     const double* wr = W + (size_t)min(col, dim - 1) * dim;
     for (int k0 = 0; k0 < dim; k0 += 16) {
-      const int k = k0 + 4 * q16;
       double b[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) b[e] = (col < dim && k + e < dim) ? wr[k + e] : 0.0;
+      for (int e = 0; e < 4; ++e) {
+        const int k = k0 + 4 * e + q16;
+        b[e] = (col < dim && k < dim) ? wr[k] : 0.0;
+      }
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(t[l16 * ld + k + e], b[e], acc[u], 0, 0, 0);
+        acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(t[l16 * ld + k0 + 4 * e + q16], b[e], acc[u],
+                                                      0, 0, 0);
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) ss[r] += acc[u][r] * acc[u][r];
   }
+  __syncthreads();  // the centred rows are consumed
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
+  for (int u = 0; u < LN_T; ++u)
+    if (w + 4 * u < nt)
 #pragma unroll
-    for (int o = 8; o >= 1; o >>= 1) ss[r] += __shfl_xor(ss[r], o, 16);
-    if (l16 == 0) ssw[w][4 * r + q16] = ss[r];
-  }
+      for (int r = 0; r < 4; ++r) t[(4 * r + q16) * ld + 16 * (w + 4 * u) + l16] = acc[u][r];
   __syncthreads();
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = 4 * r + q16;
-    const double s = (ssw[0][row] + ssw[1][row]) + (ssw[2][row] + ssw[3][row]);
-    const double inv = s > 0.0 ? 1.0 / sqrt(s) : 0.0;
-#pragma unroll
-    for (int u = 0; u < LN_T; ++u) {
-      const int col = 16 * (w + 4 * u) + l16;
-      if (col < dim && r0 + row < n) Y[(r0 + row) * dim + col] = (float)(acc[u][r] * inv);
-    }
+  for (int r = 4 * w; r < 4 * w + 4; ++r) {
+    double ss = 0.0;
+    for (int d = lane; d < dim; d += 64) ss += t[r * ld + d] * t[r * ld + d];
+    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+    const double inv = ss > 0.0 ? 1.0 / sqrt(ss) : 0.0;
+    if (r0 + r < n)
+      for (int d = lane; d < dim; d += 64) Y[(r0 + r) * dim + d] = (float)(t[r * ld + d] * inv);
   }
 }
 
