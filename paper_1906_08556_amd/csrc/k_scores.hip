@@ -35,25 +35,29 @@ __device__ inline int64_t batch(int64_t F, const int* Fdev, int64_t fcap) {
 
 // One workgroup unit: 16 NF frames x 64 components, a block of 16 components
 // per wave.  Units of one frame group are consecutive, so the XCDs (workgroups
-// are dealt to them in turn) each keep one part of W in their L2.  A unit at
-// NF = 1 takes 238 steps of 2 MFMAs (15k cycles at one wave per SIMD, bound by
-// the latency of the chain); larger NF use each coefficient NF times.
+// are dealt to them in turn) each keep one part of W in their L2.  The features
+// of a slab of 64 / NF chunks are formed once for the four waves and kept in LDS
+// in operand order; the matrix cores then take one 8-byte read per two MFMAs
+// (formed by every wave for itself, the lookups and products took longer than
+// the MFMAs).  C = 2048, D = 60: 100 frames 36 us (60 us), 1013 frames 130 us (238 us); at NF = 1 the chain of 474 dependent MFMAs is 6 us.
 template <int NF>
 __global__ void __launch_bounds__(256)
 k_scores_f32(const float* __restrict__ X, int64_t F, int D, const float* __restrict__ shift,
              const float* __restrict__ W, int C, int Cpad, int Kpad,
              const uint16_t* __restrict__ pairs, const int* __restrict__ Fdev,
              const int* __restrict__ flist, int64_t fcap, float* __restrict__ scores) {
+  constexpr int SQ = 64 / NF;  // chunks per slab
   extern __shared__ float sm[];
   const int DS = (D + 1) | 1, nq = Kpad / 8;
-  float* xs = sm;                                            // [16 NF][DS]
+  float2* fe = reinterpret_cast<float2*>(sm);                      // [SQ][NF][64]
+  float* xs = sm + 2 * 64 * 64;                                    // [16 NF][DS]
   uint32_t* tab = reinterpret_cast<uint32_t*>(xs + 16 * NF * DS);  // [nq][4]
   const int64_t n = batch(F, Fdev, fcap);
   const int ncg = (C + 63) / 64;
   const int64_t units = (n + 16 * NF - 1) / (16 * NF) * ncg;
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
-  // lane group g takes features k0 = 4 (g % 2) + g / 2 and k0 + 2 of a chunk
-  const int k0 = 4 * (g & 1) + (g >> 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // lane group g takes features 4 (g % 2) + g / 2 and the next but one of a chunk
   if ((int64_t)blockIdx.x < units)
     for (int i = tid; i < nq * 4; i += 256) {
       const int k = 8 * (i >> 2) + 4 * (i & 1) + ((i >> 1) & 1);
@@ -61,7 +65,7 @@ k_scores_f32(const float* __restrict__ X, int64_t F, int D, const float* __restr
     }
   for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
     const int64_t f0 = u / ncg * (16 * NF);
-    const int c0 = (int)(u % ncg) * 64 + (tid >> 6) * 16;
+    const int c0 = (int)(u % ncg) * 64 + wave * 16;  // Cpad is a multiple of 256
     __syncthreads();  // the previous unit's frames are consumed
     for (int i = tid; i < 16 * NF * (D + 1); i += 256) {
       const int fr = i / (D + 1), a = i - fr * (D + 1);
@@ -70,42 +74,56 @@ k_scores_f32(const float* __restrict__ X, int64_t F, int D, const float* __restr
       if (a > 0 && f < n) v = X[(flist ? flist[f] : f) * D + a - 1] - shift[a - 1];
       xs[fr * DS + a] = v;
     }
-    __syncthreads();
-    if (c0 >= C) continue;
-    const float* w = W + ((size_t)c0 + l16) * 8 + k0;  // Cpad is a multiple of 256
     const size_t ws = (size_t)Cpad * 8;
-    const float* xf = xs + l16 * DS;
+    // a lane's two coefficients out of one 16-byte load: as two loads of 4 bytes at
+    // a stride of 32 the cache lookups of a chunk take longer than its MFMAs
+    const unsigned wl = l16 * 8 + 4 * (g & 1);
+    const bool odd = g >> 1;
     floatx4 acc[NF];
 #pragma unroll
     for (int j = 0; j < NF; ++j) acc[j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-    constexpr int PF = 8;  // chunks requested ahead (L2 latency against 64 NF cycles per chunk)
-    float wa[PF], wb[PF];
+    // chunks requested ahead (L2 latency against 64 NF cycles per chunk)
+    constexpr int PF = NF == 4 ? 4 : 8;
+    const float* const wend = W + (size_t)(nq - 1) * ws + (size_t)c0 * 8;
+    const float* wn = W + (size_t)c0 * 8;  // the next chunk to request; stays at the last
+    float4 wv[PF];
+    auto request = [&](int p) {
+      wv[p] = *reinterpret_cast<const float4*>(wn + wl);
+      wn = wn < wend ? wn + ws : wend;
+    };
 #pragma unroll
-    for (int p = 0; p < PF; ++p) {
-      wa[p] = w[min(p, nq - 1) * ws];
-      wb[p] = w[min(p, nq - 1) * ws + 2];
-    }
-    for (int q0 = 0; q0 < nq; q0 += PF) {
+    for (int p = 0; p < PF; ++p) request(p);
+    for (int s0 = 0; s0 < nq; s0 += SQ) {
+      __syncthreads();  // the frames are staged, the previous slab is consumed
+      // entry (chunk i / NF, frame block i % NF): a wave's 64 lanes in operand order
+#pragma unroll 4
+      for (int i = wave; i < 64; i += 4) {
+        const int q = min(s0 + i / NF, nq - 1);
+        const uint32_t t = tab[q * 4 + g];
+        const float* x = xs + ((i % NF) * 16 + l16) * DS;
+        fe[i * 64 + lane] = make_float2(x[t & 0xff] * x[(t >> 8) & 0xff],
+                                        x[(t >> 16) & 0xff] * x[t >> 24]);
+      }
+      __syncthreads();
+      const int q1 = min(s0 + SQ, nq);
+      for (int q0 = s0; q0 < q1; q0 += PF) {
+        const float2* fq = fe + (q0 - s0) * NF * 64 + lane;
+        float2 b[PF][NF];
 #pragma unroll
-      for (int p = 0; p < PF; ++p) {
-        const int q = q0 + p;
-        const float a0 = q < nq ? wa[p] : 0.0f, a1 = q < nq ? wb[p] : 0.0f;
-        const uint32_t t = tab[min(q, nq - 1) * 4 + g];
-        const int qn = min(q + PF, nq - 1);
-        wa[p] = w[qn * ws];
-        wb[p] = w[qn * ws + 2];
-        if (q < nq) {
+        for (int p = 0; p < PF; ++p)
 #pragma unroll
-          for (int j = 0; j < NF; ++j) {
-            const float* x = xf + j * 16 * DS;
-            acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, x[t & 0xff] * x[(t >> 8) & 0xff],
-                                                          acc[j], 0, 0, 0);
-          }
+          for (int j = 0; j < NF; ++j) b[p][j] = fq[(p * NF + j) * 64];
 #pragma unroll
-          for (int j = 0; j < NF; ++j) {
-            const float* x = xf + j * 16 * DS;
-            acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, x[(t >> 16) & 0xff] * x[t >> 24],
-                                                          acc[j], 0, 0, 0);
+        for (int p = 0; p < PF; ++p) {
+          const float a0 = odd ? wv[p].y : wv[p].x, a1 = odd ? wv[p].w : wv[p].z;
+          request(p);
+          if (q0 + p < nq) {
+#pragma unroll
+            for (int j = 0; j < NF; ++j)
+              acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b[p][j].x, acc[j], 0, 0, 0);
+#pragma unroll
+            for (int j = 0; j < NF; ++j)
+              acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b[p][j].y, acc[j], 0, 0, 0);
           }
         }
       }
@@ -114,7 +132,7 @@ k_scores_f32(const float* __restrict__ X, int64_t F, int D, const float* __restr
 #pragma unroll
     for (int j = 0; j < NF; ++j) {
       const int64_t f = f0 + 16 * j + l16;
-      if (f < n)
+      if (f < n && c0 < C)
         *reinterpret_cast<float4*>(scores + f * Cpad + c0 + 4 * g) =
             make_float4(acc[j][0], acc[j][1], acc[j][2], acc[j][3]);
     }
@@ -255,6 +273,8 @@ size_t scores_lds(int nf16, int D, int Kpad) {
   return sizeof(float) * ((size_t)16 * nf16 * ((D + 1) | 1) + (size_t)Kpad / 2);
 }
 
+constexpr size_t kSlabBytes = 64 * 64 * sizeof(float2);
+
 }  // namespace
 
 int64_t scores_frames(const ivx_ctx* ctx) {
@@ -274,11 +294,16 @@ void launch_scores_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hip
         X, F, D, ctx->shift, ctx->W16, C, ctx->Cpad, Kpad, ctx->pairs, Fdev, flist, fcap,
         ctx->scores);
   } else {
-    // frames per wave: as many as leave four workgroups per CU
+    // 16 frames per wave while four workgroups per CU hold all (also for the
+    // left-over frames of the bound, whose count only the device knows), else 64,
+    // which read W a quarter as often.  C = 2048, D = 60, whole selection in us
+    // with 16 / 32 / 64 / 128 frames: 100 frames 71 / 91 / 121 / 187, 512 frames
+    // 116 / 123 / 138 / 205, 1013 frames 176 / 184 / 169 / 208, 4000 frames 506 /
+    // 501 / 451 / 484.
     auto units = [&](int nf) { return (Fm + 16 * nf - 1) / (16 * nf) * ((C + 63) / 64); };
-    const int nf = units(4) >= 4 * (int64_t)ctx->ncu ? 4 : units(2) >= 4 * (int64_t)ctx->ncu ? 2 : 1;
-    auto* k = nf == 4 ? &k_scores_f32<4> : nf == 2 ? &k_scores_f32<2> : &k_scores_f32<1>;
-    k<<<(unsigned)std::min(units(nf), most), 256, scores_lds(nf, D, Kpad), s>>>(
+    const int nf = Fdev || units(1) <= 4 * (int64_t)ctx->ncu ? 1 : 4;
+    auto* k = nf == 4 ? &k_scores_f32<4> : &k_scores_f32<1>;
+    k<<<(unsigned)std::min(units(nf), most), 256, scores_lds(nf, D, Kpad) + kSlabBytes, s>>>(
         X, F, D, ctx->shift, ctx->Wexp, C, ctx->Cpad, Kpad, ctx->pairs, Fdev, flist, fcap,
         ctx->scores);
   }
