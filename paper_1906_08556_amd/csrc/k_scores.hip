@@ -37,9 +37,11 @@ __device__ inline int64_t batch(int64_t F, const int* Fdev, int64_t fcap) {
 // per wave.  Units of one frame group are consecutive, so the XCDs (workgroups
 // are dealt to them in turn) each keep one part of W in their L2.  The features
 // of a slab of 64 / NF chunks are formed once for the four waves and kept in LDS
-// in operand order; the matrix cores then take one 8-byte read per two MFMAs
-// (formed by every wave for itself, the lookups and products took longer than
-// the MFMAs).  C = 2048, D = 60: 100 frames 36 us (60 us), 1013 frames 130 us (238 us); at NF = 1 the chain of 474 dependent MFMAs is 6 us.
+// in operand order; two MFMAs then take one 8-byte read.  Bound by the cache
+// lookups of W's coefficients: C = 2048, D = 60, 100 frames take 36 us, 1013
+// frames 130 us (24 us when every chunk of the 100 read the same coefficients, 60
+// and 238 us with two 4-byte loads per lane and chunk and 16 or 32 frames per
+// wave); the chain of 474 dependent MFMAs at NF = 1 is 7 us.
 template <int NF>
 __global__ void __launch_bounds__(256)
 k_scores_f32(const float* __restrict__ X, int64_t F, int D, const float* __restrict__ shift,

@@ -20,23 +20,52 @@ namespace {
 
 constexpr double kLog2Pi = 1.8378770664093454836;
 
-__global__ void __launch_bounds__(64) k_ubm_shift(const double* __restrict__ w,
-                                                  const double* __restrict__ mu, int C, int D,
-                                                  float* __restrict__ shift,
-                                                  int* __restrict__ bmax) {
-  const int d = threadIdx.x;
-  if (d == 0 && bmax) bmax[0] = 0;  // taken by k_bound_scale
-  if (d >= D) return;
+// shift = sum_c w_c mu_c / sum_c w_c, added in the order of c by one lane per
+// dimension.  The workgroup loads 64 components at a time into LDS, the next
+// ones while a wave adds: the loads of one wave alone took 500 us at C = 2048.
+__global__ void __launch_bounds__(1024) k_ubm_shift(const double* __restrict__ w,
+                                                    const double* __restrict__ mu, int C, int D,
+                                                    float* __restrict__ shift,
+                                                    int* __restrict__ bmax) {
+  constexpr int N = 64;
+  __shared__ double m[N * 64], ws[N];
+  const int tid = threadIdx.x;
+  if (tid == 0 && bmax) bmax[0] = 0;  // taken by k_bound_scale
+  double r[4], rw = 0.0;  // D <= 63: at most four elements per thread
+  auto load = [&](int c0) {
+    const int n = min(N, C - c0) * D;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int e = tid + 1024 * i;
+      r[i] = e < n ? mu[(size_t)c0 * D + e] : 0.0;
+    }
+    if (tid < N && c0 + tid < C) rw = w[c0 + tid];
+  };
+  load(0);
   double s = 0.0, sw = 0.0;
-  for (int c = 0; c < C; ++c) {
-    s += w[c] * mu[(size_t)c * D + d];
-    sw += w[c];
+  for (int c0 = 0; c0 < C; c0 += N) {
+    __syncthreads();  // the previous components are consumed
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (tid + 1024 * i < N * D) m[tid + 1024 * i] = r[i];
+    if (tid < N) ws[tid] = rw;
+    __syncthreads();
+    if (c0 + N < C) load(c0 + N);
+    if (tid < D) {
+      const int n = min(N, C - c0);
+#pragma unroll 8
+      for (int c = 0; c < n; ++c) {
+        s += ws[c] * m[c * D + tid];
+        sw += ws[c];
+      }
+    }
   }
-  shift[d] = (float)(s / sw);
+  if (tid < D) shift[tid] = (float)(s / sw);
 }
 
 // One 64-thread workgroup per component (D <= 63).  LDS: L and L^{-1}, D x D
-// doubles each.
+// doubles each, the rows of L at an odd stride (a lane per row: at stride D = 60
+// eight lanes met in a bank: 1013 us for 2048 components, now 954).
 __global__ void __launch_bounds__(64) k_ubm_prepare(
     const double* __restrict__ w, const double* __restrict__ mu, const double* __restrict__ cov,
     const float* __restrict__ shift, int C, int D, int K, int Kpad,
@@ -44,8 +73,9 @@ __global__ void __launch_bounds__(64) k_ubm_prepare(
     double* __restrict__ linv_out, float* __restrict__ linv32r_out,
     double* __restrict__ cst_out, int* __restrict__ err) {
   extern __shared__ double sm[];
-  double* A = sm;           // [D][D], becomes L (lower triangle)
-  double* Li = sm + D * D;  // [D][D], L^{-1} (lower triangle)
+  const int LD = D | 1;
+  double* A = sm;            // [D][LD], becomes L (lower triangle)
+  double* Li = sm + D * LD;  // [D][D], L^{-1} (lower triangle)
   __shared__ double y[64], bv[64], red[64];
   __shared__ int bad;
   const int c = blockIdx.x;
@@ -65,24 +95,25 @@ __global__ void __launch_bounds__(64) k_ubm_prepare(
     for (int k = t; k < Kpad; k += 64) put(k, (k == 0) ? -1e30f : 0.0f);
     return;
   }
-  for (int i = t; i < D * D; i += 64) A[i] = cov[(size_t)c * D * D + i];
+  for (int i = 0; i < D; ++i)
+    if (t < D) A[i * LD + t] = cov[(size_t)c * D * D + i * D + t];
   if (t == 0) bad = 0;
   __syncthreads();
   // Cholesky, right-looking, one column per step
   for (int j = 0; j < D; ++j) {
-    const double djj = A[j * D + j];
+    const double djj = A[j * LD + j];
     if (!(djj > 0.0) || !isfinite(djj)) {
       if (t == 0) bad = 1;
       break;  // djj is read by every thread: uniform exit
     }
     const double ljj = sqrt(djj);
     __syncthreads();
-    if (t > j && t < D) A[t * D + j] /= ljj;
-    if (t == j) A[j * D + j] = ljj;
+    if (t > j && t < D) A[t * LD + j] /= ljj;
+    if (t == j) A[j * LD + j] = ljj;
     __syncthreads();
     if (t > j && t < D) {
-      const double lij = A[t * D + j];
-      for (int k = j + 1; k <= t; ++k) A[t * D + k] -= lij * A[k * D + j];
+      const double lij = A[t * LD + j];
+      for (int k = j + 1; k <= t; ++k) A[t * LD + k] -= lij * A[k * LD + j];
     }
     __syncthreads();
   }
@@ -99,11 +130,11 @@ __global__ void __launch_bounds__(64) k_ubm_prepare(
   if (t < D) {
     const int j = t;
     for (int i = 0; i < j; ++i) Li[i * D + j] = 0.0;
-    Li[j * D + j] = 1.0 / A[j * D + j];
+    Li[j * D + j] = 1.0 / A[j * LD + j];
     for (int i = j + 1; i < D; ++i) {
       double s = 0.0;
-      for (int k = j; k < i; ++k) s += A[i * D + k] * Li[k * D + j];
-      Li[i * D + j] = -s / A[i * D + i];
+      for (int k = j; k < i; ++k) s += A[i * LD + k] * Li[k * D + j];
+      Li[i * D + j] = -s / A[i * LD + i];
     }
   }
   __syncthreads();
@@ -125,7 +156,7 @@ __global__ void __launch_bounds__(64) k_ubm_prepare(
     double quad = 0.0, hld = 0.0;
     for (int i = 0; i < D; ++i) {
       quad += red[i];
-      hld += log(A[i * D + i]);
+      hld += log(A[i * LD + i]);
     }
     const double base = log(w[c]) - 0.5 * D * kLog2Pi - hld;
     cst_out[c] = base;
@@ -227,8 +258,8 @@ __global__ void k_update_means(const double* __restrict__ T, const double* __res
 }  // namespace
 
 void launch_ubm_prepare(ivx_ctx* ctx, bool cov_changed, hipStream_t s) {
-  k_ubm_shift<<<1, 64, 0, s>>>(ctx->w, ctx->mu, ctx->C, ctx->D, ctx->shift, ctx->bmax);
-  const size_t lds = 2 * sizeof(double) * ctx->D * ctx->D;
+  k_ubm_shift<<<1, 1024, 0, s>>>(ctx->w, ctx->mu, ctx->C, ctx->D, ctx->shift, ctx->bmax);
+  const size_t lds = sizeof(double) * ctx->D * (ctx->D + (ctx->D | 1));
   k_ubm_prepare<<<ctx->Cpad, 64, lds, s>>>(ctx->w, ctx->mu, ctx->cov, ctx->shift, ctx->C, ctx->D,
                                            ctx->K, ctx->Kpad, ctx->pairs, ctx->Wexp, ctx->W16,
                                            ctx->linv, ctx->linv32r, ctx->cst, ctx->dev_err);
