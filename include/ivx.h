@@ -396,10 +396,12 @@ ivx_status ivx_selector_counts(ivx_ctx* ctx, int64_t* fallback_frames, int64_t* 
 
 /* Launch shapes of the hot-path kernels.  Every choice computes the same
  * result (up to FP32 summation order in the split GEMM).
- *   frame_ncb       launch shape of the FP32 frame GEMM: 8 (256 components
- *                   per launch, one 32-frame block per wave), 4 (128
- *                   components) or 2 (128 components, two frame blocks per
- *                   wave)
+ *   frame_ncb       FP32 frame stage: 8 preselects components by a bound
+ *                   (large batches) or splits the scores over components
+ *                   (small ones) where the model allows it, else all
+ *                   components 256 at a time, one 32-frame block per wave;
+ *                   4 (128 components) and 2 (128 components, two frame
+ *                   blocks per wave) always score all components
  *   frame_ncb_bf16  the same for the BF16 split form
  *   b_split         K-splits of the linear-term GEMM b = p + F V (0: chosen
  *                   from the grid size; else 1..max)

@@ -198,8 +198,6 @@ ivx_status ivx_create(const ivx_dims* dims, int device, ivx_ctx** out) {
     A(dalloc(&c->bmax, 1));
     A(dalloc(&c->Wf, (size_t)c->Cpad / 2 * 512 * 8));
     A(dalloc(&c->cb, c->Cpad));
-    c->sweep_frames = bound_sweep_frames(c->Cpad, (int64_t)F);
-    A(dalloc(&c->sums16, (size_t)c->sweep_frames * c->Cpad));
     A(dalloc(&c->lquad, C * 4096));
   }
   A(dalloc(&c->pairs, (size_t)c->Kpad));
@@ -253,6 +251,16 @@ ivx_status ivx_create(const ivx_dims* dims, int device, ivx_ctx** out) {
   A(dalloc(&c->mvec, 4 * R));
   A(dalloc(&c->mstat, C));
   A(dalloc(&c->dev_err, 4));
+  if (c->Wf) {  // last: with less memory left than asked for, fewer frames per pass
+    c->sweep_frames = bound_sweep_frames(c->Cpad, (int64_t)F);
+    while (ok && c->sweep_frames > 4096 &&
+           dalloc(&c->sums16, (size_t)c->sweep_frames * c->Cpad) != hipSuccess) {
+      (void)hipGetLastError();
+      c->sums16 = nullptr;
+      c->sweep_frames = c->sweep_frames / 1024 * 512;
+    }
+    if (!c->sums16) A(dalloc(&c->sums16, (size_t)c->sweep_frames * c->Cpad));
+  }
   if (!ok) {
     ivx_destroy(c);
     (void)hipGetLastError();
