@@ -28,6 +28,7 @@ sys.path.insert(0, ROOT)
 METRIC = "TV EM utts/s + frame posteriors/s at C=2048,D=60,R=400 vs FP32 plain"
 HBM_PEAK_GBS = 8000.0
 FP32_MFMA_PEAK_TFLOPS = 157.3
+FP64_MFMA_PEAK_TFLOPS = 78.6
 # BF16 MFMA products per FP32 product in the BF16 frame filter (operands split
 # into high and low BF16 parts: hi*hi + hi*lo + lo*hi)
 BF16_PRODUCTS = 3
@@ -676,22 +677,39 @@ def main():
     frames_per_s = F * K / (phase["frame"] / 1e3)
     em_utts_per_s = U * K / (phase["em"] / 1e3)
 
-    # roofline of the dominant kernel: the expanded-feature frame GEMM, one
-    # persistent launch per pass that scores every frame against all C
-    # components (2 K C FLOPs per frame, the method's count)
+    # roofline of the dominant kernel.  With the default launch shape the frame
+    # stage scores only the components that a bound cannot exclude (most of the
+    # method's 2 K C FLOPs per frame are never executed), and the FP64
+    # accumulator products A += N^T Psi, Cc += F^T phi dominate; any other shape
+    # runs the expanded-feature frame GEMM over all C components in one launch.
     Kexp = (D + 1) * (D + 2) // 2
     tune_now = ctx.tuning_get()
     flop_per_frame = 2.0 * Kexp * C
     fs_ms, fs_calls = prof["frame_select"]
     fs_avg_s = fs_ms / max(fs_calls, 1) / 1e3
-    achieved = flop_per_frame * F / fs_avg_s / 1e12
-    roof = {"kernel": "k_frame_tile", "bound": "mfma", "achieved": round(achieved, 2),
-            "peak": FP32_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
-            "frac": round(achieved / FP32_MFMA_PEAK_TFLOPS, 4),
-            "traffic": measured_traffic("k_frame_tile", f"shape{args.shape}", F),
-            "avg_launch_ms": round(fs_avg_s * 1e3, 3), "launches_per_step": fs_calls // K,
-            "flop_per_frame_per_launch": flop_per_frame, "frames_per_launch": F,
-            "components_per_launch": C}
+
+    def dense(ncb):
+        return ncb != 8 or tune_now["frame_direct"] != 0 or C < 512 or not 32 <= D <= 62
+
+    if dense(tune_now["frame_ncb"]):
+        achieved = flop_per_frame * F / fs_avg_s / 1e12
+        roof = {"kernel": "k_frame_tile", "bound": "mfma", "achieved": round(achieved, 2),
+                "peak": FP32_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
+                "frac": round(achieved / FP32_MFMA_PEAK_TFLOPS, 4),
+                "traffic": measured_traffic("k_frame_tile", f"shape{args.shape}", F),
+                "avg_launch_ms": round(fs_avg_s * 1e3, 3), "launches_per_step": fs_calls // K,
+                "flop_per_frame_per_launch": flop_per_frame, "frames_per_launch": F,
+                "components_per_launch": C}
+    else:
+        acc_ms = prof["accumulate"][0] / K
+        acc_flop = U * (1.0 * C * R * (R + 1) + 2.0 * C * D * R)
+        achieved = acc_flop / (acc_ms / 1e3) / 1e12
+        roof = {"kernel": "k_gemm64_tn_128", "bound": "mfma", "achieved": round(achieved, 2),
+                "peak": FP64_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
+                "frac": round(achieved / FP64_MFMA_PEAK_TFLOPS, 4),
+                "group_ms_per_step": round(acc_ms, 3), "flop_per_step": acc_flop,
+                "group": "both products, the conversion of Phi to FP64 and the column sums",
+                "frame_stage_ms_per_step": round(fs_ms / K, 3)}
     log("[bench] FP32 kernel groups (ms per step): " + ", ".join(
         f"{k}={v[0] / K:.2f}" for k, v in prof.items() if v[1]))
     log(f"[bench] objective after last step: {obj.item():.6e}")
@@ -720,13 +738,15 @@ def main():
                 "steps": Ks,
                 "frame_posteriors_per_s": round(F * Ks / (ph16["frame"] / 1e3), 1),
                 "tv_em_utts_per_s": round(U * Ks / (ph16["em"] / 1e3), 3),
-                "frame_kernel": {"kernel": "k_frame_tile_bf16", "achieved_bf16_tflops": round(ach16, 2),
-                                 "peak": bf16_peak, "frac": round(ach16 / bf16_peak, 4),
-                                 "flops_counted": "method (2 K per frame and component, once)",
-                                 "mfma_products_per_method_product": BF16_PRODUCTS,
-                                 "hardware_mfma_tflops": round(BF16_PRODUCTS * ach16, 2),
-                                 "avg_launch_ms": round(fs16_avg_s * 1e3, 3),
-                                 "components_per_launch": C},
+                "frame_stage_ms_per_step": round(fs16_ms / Ks, 3),
+                **({"frame_kernel": {
+                    "kernel": "k_frame_tile_bf16", "achieved_bf16_tflops": round(ach16, 2),
+                    "peak": bf16_peak, "frac": round(ach16 / bf16_peak, 4),
+                    "flops_counted": "method (2 K per frame and component, once)",
+                    "mfma_products_per_method_product": BF16_PRODUCTS,
+                    "hardware_mfma_tflops": round(BF16_PRODUCTS * ach16, 2),
+                    "avg_launch_ms": round(fs16_avg_s * 1e3, 3),
+                    "components_per_launch": C}} if dense(tune_now["frame_ncb_bf16"]) else {}),
                 "vs_fp32_form_first_iteration": {
                     "ivector_min_cosine": float(cos.min()),
                     "objective_rel_diff": abs(outs[1][1] - outs[0][1]) / abs(outs[0][1])}}
