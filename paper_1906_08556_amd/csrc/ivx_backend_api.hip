@@ -304,10 +304,12 @@ ivx_status ivx_backend_plda_score(ivx_backend* b, const double* mu, const double
     Z2 = b->Z2;
   }
   be_plda_coef(psi, d, b->coef, s);
-  // Most pairs of small sets asked for: all pairs as one FP64 matrix product,
-  // then a gather.  A pair of the product costs about 1/40 of a trial on its
-  // own (all 719k pairs of 1200 vectors, d = 200: 263 us one by one).
-  if (n1 * n2 <= b->pm_elems && T >= n1 * n2 / 16 && n1 <= 64 * 65535) {
+  // Many of the pairs of small sets asked for: all pairs as one FP64 matrix
+  // product, then a gather.  A pair of the product costs about 1/40 of a trial
+  // on its own, but its launches and its chain take as long as some 90k trials
+  // (d = 200, projections included: 80k trials 51 us one by one, 54 us so; 719k
+  // trials 290 and 68 us).
+  if (n1 * n2 <= b->pm_elems && T >= n1 * n2 / 16 && T >= 98304 && n1 <= 64 * 65535) {
     be_plda_matrix(b->Z1, n1, Z2, n2, d, b->coef, b->pq, b->pm, s);
     be_plda_gather(b->pm, n1, n2, trials, T, scores, b->flags + 2, s);
   } else {

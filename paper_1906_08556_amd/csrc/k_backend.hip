@@ -278,34 +278,50 @@ k_gather_cols(const double* __restrict__ src, int ld, const int* __restrict__ id
   if (vals && e < keep) vals[e] = w[idx[e]];
 }
 
-// y = x - mean (mean optional) scaled to unit length; one wave per row.
+// y = W (x - mean) (W optional) scaled to unit length; one wave per row,
+// four rows per workgroup, the centred and whitened rows staged in LDS.
 constexpr int LN_MAX = 512;
 __global__ void __launch_bounds__(256)
 k_lnorm(const float* __restrict__ X, int64_t n, int dim, const double* __restrict__ mean,
-        float* __restrict__ Y) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= n) return;
+        const double* __restrict__ W, float* __restrict__ Y) {
+  __shared__ double t[4][LN_MAX];
+  __shared__ double y[4][LN_MAX];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int64_t row = (int64_t)blockIdx.x * 4 + wv;
+  const bool active = row < n;
+  if (active)
+    for (int d = lane; d < dim; d += 64)
+      t[wv][d] = (double)X[row * dim + d] - (mean ? mean[d] : 0.0);
+  __syncthreads();
   double ss = 0.0;
-  for (int d = lane; d < dim; d += 64) {
-    const double a = (double)X[row * dim + d] - (mean ? mean[d] : 0.0);
-    ss += a * a;
+  if (active) {
+    for (int i = lane; i < dim; i += 64) {
+      double a = t[wv][i];
+      if (W) {
+        const double* wi = W + (size_t)i * dim;
+        a = 0.0;
+        for (int d = 0; d < dim; ++d) a += wi[d] * t[wv][d];
+      }
+      y[wv][i] = a;
+      ss += a * a;
+    }
   }
   for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-  const double inv = ss > 0.0 ? 1.0 / sqrt(ss) : 0.0;
-  for (int d = lane; d < dim; d += 64)
-    Y[row * dim + d] = (float)(((double)X[row * dim + d] - (mean ? mean[d] : 0.0)) * inv);
+  if (active) {
+    const double inv = ss > 0.0 ? 1.0 / sqrt(ss) : 0.0;
+    for (int i = lane; i < dim; i += 64) Y[row * dim + i] = (float)(y[wv][i] * inv);
+  }
 }
 
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
-// The same with a whitening matrix, 16 rows per workgroup: W (x - mean) on FP64
+// The same with W, 16 rows per workgroup: W (x - mean) on FP64
 // MFMA (16 x 16 x 4), the centred rows in LDS, every wave the output columns
 // 16 (wave + 4 t).  The matrix cores add the products one by one in the order of
 // the columns, and the squares are added as the wave per row of k_lnorm would,
-// so a row is the one that a lane per output forms.  1200 rows of 400: 113 us
-// (bound by one workgroup's chain of MFMAs, 75 workgroups), a lane per output
-// 284 us (it read a column of strided entries of W for every row).
+// so a row is the one that a lane per output forms.  1200 rows of 400: 96 us
+// (75 workgroups, bound by the cache lookups of their reads of W: 32 contiguous
+// bytes per row and instruction), a lane per output 284 us (8 bytes).
 constexpr int LN_T = LN_MAX / 64;  // output tiles per wave
 __global__ void __launch_bounds__(256)
 k_lnorm_white(const float* __restrict__ X, int64_t n, int dim, const double* __restrict__ mean,
@@ -321,25 +337,33 @@ k_lnorm_white(const float* __restrict__ X, int64_t n, int dim, const double* __r
   __syncthreads();
   const int nt = (dim + 15) / 16;
   doublex4 acc[LN_T];
+  double b[LN_T][4];  // a tile's entries of W, loaded while the other tiles multiply
+  auto row = [&](int u, int k0) {  // columns >= dim of Y are not stored
+    const double* wr = W + (size_t)min(16 * (w + 4 * u) + l16, dim - 1) * dim;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int k = k0 + 4 * e + q16;
+      const double v = wr[min(k, dim - 1)];
+      b[u][e] = k < dim ? v : 0.0;
+    }
+  };
 #pragma unroll
   for (int u = 0; u < LN_T; ++u) {
-    const int tile = w + 4 * u;
     acc[u] = doublex4{0.0, 0.0, 0.0, 0.0};
-    if (tile >= nt) continue;
-    const int col = 16 * tile + l16;
-    const double* wr = W + (size_t)min(col, dim - 1) * dim;
-    for (int k0 = 0; k0 < dim; k0 += 16) {
-      double b[4];
+    if (w + 4 * u < nt) row(u, 0);
+  }
+  for (int k0 = 0; k0 < dim; k0 += 16) {
+    double a[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int k = k0 + 4 * e + q16;
-        b[e] = (col < dim && k < dim) ? wr[k] : 0.0;
+    for (int e = 0; e < 4; ++e) a[e] = t[l16 * ld + k0 + 4 * e + q16];
+#pragma unroll
+    for (int u = 0; u < LN_T; ++u)
+      if (w + 4 * u < nt) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[e], b[u][e], acc[u], 0, 0, 0);
+        row(u, k0 + 16);
       }
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(t[l16 * ld + k0 + 4 * e + q16], b[e], acc[u],
-                                                      0, 0, 0);
-    }
   }
   __syncthreads();  // the centred rows are consumed
 #pragma unroll
@@ -428,8 +452,8 @@ k_plda_quad(const float* __restrict__ Z1, int64_t n1, const float* __restrict__ 
 
 // M[i][j] = c + q1_i + q2_j + sum_k b_k z1_ik z2_jk: 64 x 64 tile, FP64 MFMA,
 // a wave per 32 x 32 quarter, 16 dimensions per LDS stage.  1.44 M pairs of
-// d = 200: 46 us (361 workgroups, less than two per CU, staging with
-// conversions between barriers bounds it); 719 k trials one by one take 263 us.
+// d = 200: 43 us (361 workgroups, less than two per CU; the staging between
+// barriers bounds it); 719 k trials one by one take 263 us.
 __global__ void __launch_bounds__(256)
 k_plda_matrix(const float* __restrict__ Z1, int64_t n1, const float* __restrict__ Z2, int64_t n2,
               int d, const double* __restrict__ coef, const double* __restrict__ q,
@@ -444,14 +468,29 @@ k_plda_matrix(const float* __restrict__ Z1, int64_t n1, const float* __restrict_
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+  const int kc = tid & 15, rr = tid >> 4;  // column and first row of the thread's entries
+  float za[4], zb[4];
+  double cf = 0.0;
+  auto load = [&](int k0) {  // rows and columns beyond the edge: any, then zero
+    const int k = min(k0 + kc, d - 1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      za[i] = Z1[min(i0 + rr + 16 * i, n1 - 1) * d + k];
+      zb[i] = Z2[min(j0 + rr + 16 * i, n2 - 1) * d + k];
+    }
+    cf = coef[d + k];
+  };
+  load(0);
   for (int k0 = 0; k0 < d; k0 += 16) {
     __syncthreads();
-    for (int e = tid; e < 64 * 16; e += 256) {
-      const int r = e >> 4, k = k0 + (e & 15);
-      As[e & 15][r] = (i0 + r < n1 && k < d) ? coef[d + k] * (double)Z1[(i0 + r) * d + k] : 0.0;
-      Bs[e & 15][r] = (j0 + r < n2 && k < d) ? (double)Z2[(j0 + r) * d + k] : 0.0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool in = k0 + kc < d;
+      As[kc][rr + 16 * i] = in ? cf * (double)za[i] : 0.0;
+      Bs[kc][rr + 16 * i] = in ? (double)zb[i] : 0.0;
     }
     __syncthreads();
+    if (k0 + 16 < d) load(k0 + 16);
 #pragma unroll
     for (int ks = 0; ks < 16; ks += 4) {
       double a[2], b[2];
@@ -609,10 +648,14 @@ void be_gather_cols(const double* src, int ld, const int* idx, int rows, int kee
 void be_lnorm(const float* X, int64_t n, int dim, const double* mean, const double* W, float* Y,
               hipStream_t s) {
   if (n <= 0) return;
-  if (W)
+  // the matrix-core form from where its reads of W pay for its longer chain (a
+  // call in us, lane per output / matrix cores: dimension 60 10.1 / 10.6, 150
+  // 15.7 / 16.6, 250 33 / 27, 400 142 / 86), or where k_lnorm would need a second
+  // round of workgroups (1500 rows of 150: 27 / 17)
+  if (W && (dim > 192 || n > 1024))
     k_lnorm_white<<<(unsigned)((n + 15) / 16), 256, lnorm_lds(dim), s>>>(X, n, dim, mean, W, Y);
   else
-    k_lnorm<<<(unsigned)((n + 3) / 4), 256, 0, s>>>(X, n, dim, mean, Y);
+    k_lnorm<<<(unsigned)((n + 3) / 4), 256, 0, s>>>(X, n, dim, mean, W, Y);
 }
 
 bool be_set_attributes() {
