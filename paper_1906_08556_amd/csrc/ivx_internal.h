@@ -194,7 +194,7 @@ struct ivx_ctx {
   int* bmax = nullptr;        // [1] largest magnitude of both (float bits)
   _Float16* Wf = nullptr;     // [Cpad/2][2][4][64][8] scaled W_c in MFMA fragment order
   float2* cb = nullptr;       // [Cpad] scaled constants of the bound's test
-  uint16_t* sums16 = nullptr;  // [sweep_frames][Cpad] 16-row sums between the sweeps
+  uint16_t* sums16 = nullptr;  // [sweep_frames][Cpad] 16-row sums between the sweeps, or null
   int64_t sweep_frames = 0;    // frames per pass of the sweeps
   float* lquad = nullptr;     // [C][16][64][4] L_c^{-1} in FP32, four columns per row
   double* cst = nullptr;      // [C] log w_c - D/2 log 2pi - sum_i log L_c[i,i]

@@ -338,7 +338,7 @@ k_bound_frames(const float* __restrict__ X, int64_t F, int D, const float* __res
 // long as the MFMAs.  Sweep 2 reads the sums (16 GB) and forms the second 16
 // rows of 43 % of the blocks: 11.1 ms with 8 pairs per stage, 12.7 with 4 (its
 // stages are short, the loads of the next must be complete at their end), 22 ms
-// when it formed the first 16 rows again.
+// when it forms the first 16 rows again (no room for the sums).
 
 // 16 bytes per lane from device memory straight into LDS: lane l's at dst + 16 l
 // (dst wave-uniform).  Complete after dma_wait() and a barrier.
@@ -364,8 +364,9 @@ __device__ inline float cut_value(uint32_t w, int half) {
   return (float)__builtin_bit_cast(cut2, w)[half];
 }
 
-// Sweep 1: the component with the largest bound (16 rows) of every frame.
-template <int FB>
+// Sweep 1: the component with the largest bound (16 rows) of every frame; KEEP:
+// the sums are kept for sweep 2.
+template <int FB, bool KEEP>
 __global__ void __launch_bounds__(64 * BW, 4)
 k_bound_best(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int64_t f0, int64_t F,
              const _Float16* __restrict__ Wf, const float2* __restrict__ cb,
@@ -420,7 +421,7 @@ k_bound_best(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
     for (int ch = 0; ch < nch; ++ch) {
       const int b = ch & 1;
       if (ch + 1 < nch) stage(ch + 1, b ^ 1);  // last read before the previous barrier
-      if (ch > 0) put(ch - 1);                 // complete by the wait below
+      if (KEEP && ch > 0) put(ch - 1);         // complete by the wait below
 #pragma unroll
       for (int i = 0; i < CH; ++i) {
         half8 a[4];
@@ -455,7 +456,7 @@ k_bound_best(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
       dma_wait();
       __syncthreads();
     }
-    put(nch - 1);
+    if (KEEP) put(nch - 1);
 #pragma unroll
     for (int fb = 0; fb < FB; ++fb) {
       const float ov = __shfl_xor(bv[fb], 32);
@@ -469,26 +470,29 @@ k_bound_best(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
 
 // Sweep 2: the components whose bound reaches the threshold M - margin, M the
 // exact score of the component of sweep 1 (in cM, best in flag).  The first 16
-// rows come from sweep 1 (the same tiles); the second 16 rows are
-// formed where any lane of the wave passes on the first 16.
+// rows come from sweep 1 (KEPT: the same tiles) or are formed again; the second
+// 16 rows are formed where any lane of the wave passes on the first 16.
 // Lists: surv [F][2][32] component ids, counts (or -1) over flag.
-template <int FB>
+template <int FB, bool KEPT>
 __global__ void __launch_bounds__(64 * BW, 4)
 k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int64_t f0, int64_t F,
              const _Float16* __restrict__ Wf, const float2* __restrict__ cb,
              const int* __restrict__ maxbits, int npair, float margin,
              const float* __restrict__ Mf, const uint2v* __restrict__ sums,
              uint16_t* __restrict__ surv, int* __restrict__ flag, const int* __restrict__ Fdev) {
-  __shared__ __attribute__((aligned(16))) uint4 st[2][CL * 256];
-  __shared__ float2 sc[2][2 * CL];
+  constexpr int NP = KEPT ? CL : CL / 2;  // pairs per stage
+  constexpr int PW = KEPT ? 256 : 512;    // staged operand of a pair: the second block, or both
+  __shared__ __attribute__((aligned(16))) uint4 st[2][NP * PW];
+  __shared__ float2 sc[2][2 * NP];
   if (Fdev && (int64_t)Fdev[0] < F) F = Fdev[0];
   constexpr int FT = 32 * BW * FB;
   const int64_t ntile = (F - f0 + FT - 1) / FT;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5, l32 = lane & 31;
-  const uint4* W4 = reinterpret_cast<const uint4*>(Wf) + (size_t)(tid >> 8) * 512 + 256 + (tid & 255);
-  const int nch = npair / CL;  // Cpad is a multiple of 256
+  const uint4* W4 = reinterpret_cast<const uint4*>(Wf) +
+                    (KEPT ? (size_t)(tid >> 8) * 512 + 256 + (tid & 255) : tid);
+  const int nch = npair / NP;  // Cpad is a multiple of 256
   for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
     const int64_t fw = f0 + tile * FT + wave * 32 * FB;
     half8 xf[FB][4];
@@ -525,17 +529,19 @@ k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
       }
       cnt[fb] = good ? 0 : SL + 1;
     }
-    // stage ch in buffer b: the second 16 rows of CL pairs and their constants
+    // stage ch in buffer b: the operands of NP pairs (512 entries per copy: two
+    // pairs' second blocks, or one pair) and their constants
     auto stage = [&](int ch, int b) {
 #pragma unroll
-      for (int j = 0; j < CL / 2; ++j)
-        dma16(W4 + (size_t)ch * CL * 512 + 1024 * j, &st[b][512 * j + wave * 64]);
-      if (tid < 2 * CL) sc[b][tid] = cb[2 * CL * ch + tid];
+      for (int j = 0; j < NP * PW / 512; ++j)
+        dma16(W4 + (size_t)ch * NP * 512 + (KEPT ? 1024 : 512) * j, &st[b][512 * j + wave * 64]);
+      if (tid < 2 * NP) sc[b][tid] = cb[2 * NP * ch + tid];
     };
-    const uint2v* ct = sums + (size_t)tile * nch * 2 * FB * (64 * BW) + tid;
+    const uint2v* ct = sums + (KEPT ? (size_t)tile * nch * 2 * FB * (64 * BW) + tid : 0);
     // half a stage's sums, loaded half a stage ahead
     uint2v w[2][FB];
     auto get = [&](int ch, int j) {
+      if (!KEPT) return;
 #pragma unroll
       for (int fb = 0; fb < FB; ++fb)
         w[j][fb] = __builtin_nontemporal_load(ct + (size_t)((2 * ch + j) * FB + fb) * (64 * BW));
@@ -552,23 +558,39 @@ k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
       if (ch + 1 < nch) stage(ch + 1, b ^ 1);  // last read before the previous barrier
       get(ch, 1);
 #pragma unroll
-      for (int i = 0; i < CL; ++i) {
+      for (int i = 0; i < NP; ++i) {
         if (i == CH) get(min(ch + 1, nch - 1), 0);
+        half8 a[4];
+        if (!KEPT) {
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks)
+            a[ks] = *reinterpret_cast<const half8*>(&st[b][i * PW + ks * 64 + lane]);
+        }
         const float2 cv = sc[b][2 * i + h];
         float t[FB], v[FB];
         bool pass[FB], any = false;
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb) {
           t[fb] = fmaf(k1[fb], cv.x, fmaf(k2[fb], cv.y, -k3[fb]));
-          v[fb] = cut_value(w[i / CH][fb][i % CH >> 1], i & 1);
+          if constexpr (KEPT) {
+            v[fb] = cut_value(w[i / CH][fb][i % CH >> 1], i & 1);
+          } else {
+            floatx16 ac = floatx16{0};
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+              ac = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ks], xf[fb][ks], ac, 0, 0, 0);
+            float sq = ac[0] * ac[0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) sq = fmaf(ac[r], ac[r], sq);
+            v[fb] = sq * rn[fb];
+          }
           pass[fb] = v[fb] <= t[fb];
           any = any || pass[fb];
         }
         if (__ballot(any) == 0) continue;
-        half8 a[4];
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
-          a[ks] = *reinterpret_cast<const half8*>(&st[b][i * 256 + ks * 64 + lane]);
+          a[ks] = *reinterpret_cast<const half8*>(&st[b][i * PW + (PW - 256) + ks * 64 + lane]);
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb) {
           if (__ballot(pass[fb]) == 0) continue;
@@ -581,7 +603,7 @@ k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
           for (int r = 1; r < 16; ++r) sq = fmaf(ac[r], ac[r], sq);
           if (pass[fb] && fmaf(sq, rn[fb], v[fb]) <= t[fb]) {
             const int64_t g = fw + 32 * fb + l32;
-            if (cnt[fb] < SL) surv[g * 64 + h * SL + cnt[fb]] = (uint16_t)(2 * (ch * CL + i) + h);
+            if (cnt[fb] < SL) surv[g * 64 + h * SL + cnt[fb]] = (uint16_t)(2 * (ch * NP + i) + h);
             ++cnt[fb];
           }
         }
@@ -1077,9 +1099,10 @@ void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipS
   ProfScope ps(ctx, PK_FRAME_SELECT, s);
   k_bound_frames<<<n16, 256, 0, s>>>(X, F, ctx->D, ctx->shift, Fdev, xh, tg);
   const bool v4 = ctx->D % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
-  // the sweeps over as many frames as their sums have room for, in equal parts
+  // the sweeps over as many frames as their sums have room for, in equal parts;
+  // without room for sums, all frames at once
   uint2v* sums = reinterpret_cast<uint2v*>(ctx->sums16);
-  const int64_t parts = (F + ctx->sweep_frames - 1) / ctx->sweep_frames;
+  const int64_t parts = sums ? (F + ctx->sweep_frames - 1) / ctx->sweep_frames : 1;
   const int64_t step = ((F + parts - 1) / parts + 511) / 512 * 512;
   for (int64_t f0 = 0; f0 < F; f0 += step) {
     const int64_t f1 = std::min(F, f0 + step), n = f1 - f0;
@@ -1092,7 +1115,9 @@ void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipS
     const unsigned nblk = (unsigned)std::min<int64_t>(two ? t2 : t1, slots);
     const int fpp = hist_frames(n, ctx->nhist);
     const unsigned np = (unsigned)((n + fpp - 1) / fpp);
-    (two ? k_bound_best<2> : k_bound_best<1>)<<<nblk, 64 * BW, 0, s>>>(
+    auto* best = !sums ? (two ? &k_bound_best<2, false> : &k_bound_best<1, false>)
+                       : (two ? &k_bound_best<2, true> : &k_bound_best<1, true>);
+    best<<<nblk, 64 * BW, 0, s>>>(
         xh, tg, f0, f1, ctx->Wf, ctx->cb, ctx->bmax, ctx->Cpad / 2, ctx->cflag, sums, Fdev);
     k_best_hist<<<np, 256, ldsc, s>>>(f0, f1, fpp, ctx->C, ctx->cflag, Fdev, ctx->hist);
     launch_hist_scan((int)np, ctx->C, ctx->hist, ctx->coff, s);
@@ -1101,7 +1126,9 @@ void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipS
     const unsigned nq1 = (unsigned)std::min<int64_t>((n + 31) / 32, 2 * (int64_t)ctx->ncu);
     (v4 ? k_bound_quad<true> : k_bound_quad<false>)<<<nq1, 256, 0, s>>>(
         X, ctx->D, ctx->coff, ctx->C, ent1, n, ctx->mu, ctx->lquad, ctx->cst, nullptr, ctx->cM);
-    (two ? k_bound_list<2> : k_bound_list<1>)<<<nblk, 64 * BW, 0, s>>>(
+    auto* list = !sums ? (two ? &k_bound_list<2, false> : &k_bound_list<1, false>)
+                       : (two ? &k_bound_list<2, true> : &k_bound_list<1, true>);
+    list<<<nblk, 64 * BW, 0, s>>>(
         xh, tg, f0, f1, ctx->Wf, ctx->cb, ctx->bmax, ctx->Cpad / 2, margin + err - 3.0f, ctx->cM,
         sums, surv, ctx->cflag, Fdev);
   }
