@@ -124,7 +124,7 @@ void ivx_destroy(ivx_ctx* ctx) {
   presel_free(ctx);
   void* ptrs[] = {ctx->w, ctx->mu, ctx->cov, ctx->shift, ctx->Wexp, ctx->W16, ctx->linv,
                   ctx->linv32r, ctx->ldense, ctx->cst, ctx->Wd, ctx->wmu, ctx->bnorm, ctx->bmax,
-                  ctx->Wf, ctx->cb, ctx->sums16, ctx->lquad,
+                  ctx->bspread, ctx->bunit, ctx->Wf, ctx->cb, ctx->sums16, ctx->lquad,
                   ctx->pairs, ctx->T, ctx->Sigma, ctx->p, ctx->bias, ctx->bias32, ctx->scores, ctx->cand, ctx->cM, ctx->cflag, ctx->post_idx,
                   ctx->post_val, ctx->frame_ll, ctx->lscore, ctx->hist, ctx->coff, ctx->ent, ctx->partial,
                   ctx->Y32, ctx->V32, ctx->Utp, ctx->Psig, ctx->sig_logdet, ctx->Lbuf, ctx->Wbuf, ctx->Psi64,
@@ -196,6 +196,8 @@ ivx_status ivx_create(const ivx_dims* dims, int device, ivx_ctx** out) {
     A(dalloc(&c->wmu, C * 32));
     A(dalloc(&c->bnorm, C));
     A(dalloc(&c->bmax, 1));
+    A(dalloc(&c->bspread, C));
+    A(dalloc(&c->bunit, 1));
     A(dalloc(&c->Wf, (size_t)c->Cpad / 2 * 512 * 8));
     A(dalloc(&c->cb, c->Cpad));
     A(dalloc(&c->lquad, C * 4096));

@@ -192,6 +192,8 @@ struct ivx_ctx {
   float* wmu = nullptr;       // [C][32] W_c (mu_c - shift)
   float2* bnorm = nullptr;    // [C] Frobenius norms of W_c and W_c (mu_c - shift)
   int* bmax = nullptr;        // [1] largest magnitude of both (float bits)
+  double2* bspread = nullptr; // [C] weight, weight times mean square per dimension
+  float* bunit = nullptr;     // [1] power of two between the features' and the bound's units
   _Float16* Wf = nullptr;     // [Cpad/2][2][4][64][8] scaled W_c in MFMA fragment order
   float2* cb = nullptr;       // [Cpad] scaled constants of the bound's test
   uint16_t* sums16 = nullptr;  // [sweep_frames][Cpad] 16-row sums between the sweeps, or null

@@ -170,23 +170,57 @@ k_bound_dirs(const double* __restrict__ linv, const double* __restrict__ cst, in
   }
 }
 
-// W_c mu'_c (mu' = mu - shift), Frobenius norms, and the largest magnitude of
-// all (bits of a non-negative float order as integers): one wave per component.
+// (w_c, w_c (tr Sigma_c + ||mu'_c||^2) / D), mu' = mu - shift: one wave per component
 __global__ void __launch_bounds__(256)
-k_bound_scale(const float* __restrict__ Wd, const double* __restrict__ mu,
-              const double* __restrict__ cst, const float* __restrict__ shift, int C, int D,
-              float* __restrict__ wmu, float2* __restrict__ norms, int* __restrict__ maxbits) {
+k_bound_spread(const double* __restrict__ w, const double* __restrict__ mu,
+               const double* __restrict__ cov, const double* __restrict__ cst,
+               const float* __restrict__ shift, int C, int D, double2* __restrict__ spread) {
   const int lane = threadIdx.x & 63, c = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (c >= C) return;
+  double v = 0.0;
+  if (lane < D) {
+    const double m = mu[(size_t)c * D + lane] - (double)shift[lane];
+    v = cov[((size_t)c * D + lane) * D + lane] + m * m;
+  }
+  v = wave_sum(v);
+  if (lane == 0) {
+    const bool ok = isfinite(cst[c]) && isfinite(v);
+    spread[c] = ok ? make_double2(w[c], w[c] * v / D) : make_double2(0.0, 0.0);
+  }
+}
+
+// The bound works in units of 2^-a of the features, 2^a bringing their root mean
+// square per dimension under the model to [2, 4), so that neither the FP16
+// range nor the least rounding term of a frame (k_bound_frames) depends on the
+// features' scale.  With the features as they come, 131,072 frames at C = 2048, D =
+// 60 took 1.50 ms at the workload's scale (a = 0) and 9.5 ms at a hundredth of it.
+// W_c mu'_c, Frobenius norms in these units, the largest magnitude of all (bits
+// of a non-negative float order as integers), 2^a: one wave per component.
+__global__ void __launch_bounds__(256)
+k_bound_scale(const float* __restrict__ Wd, const double* __restrict__ mu,
+              const double* __restrict__ cst, const float* __restrict__ shift,
+              const double2* __restrict__ spread, int C, int D, float* __restrict__ wmu,
+              float2* __restrict__ norms, int* __restrict__ maxbits, float* __restrict__ unit) {
+  const int lane = threadIdx.x & 63, c = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (c >= C) return;
+  double sw = 0.0, sv = 0.0;  // every wave for itself, in the same order
+  for (int i = lane; i < C; i += 64) {
+    sw += spread[i].x;
+    sv += spread[i].y;
+  }
+  const double rms = sqrt(wave_sum(sv) / wave_sum(sw));
+  const int a = rms > 0.0 && isfinite(rms) ? max(-60, min(60, 1 - ilogb(rms))) : 0;
+  if (c == 0 && lane == 0) unit[0] = ldexpf(1.0f, a);
+  const float iu = ldexpf(1.0f, -a);
   const double m = lane < D ? mu[(size_t)c * D + lane] - (double)shift[lane] : 0.0;
   double fro = 0.0, bm = 0.0;
   float mx = 0.0f;
   for (int i = 0; i < BR; ++i) {
     const float w = lane < D ? Wd[((size_t)c * BR + i) * 64 + lane] : 0.0f;
-    const double s = wave_sum((double)w * m);
-    fro += (double)w * w;
+    const double s = wave_sum((double)w * m), wu = (double)w * iu;
+    fro += wu * wu;
     bm += s * s;
-    mx = fmaxf(mx, fmaxf(fabsf(w), fabsf((float)s)));
+    mx = fmaxf(mx, fmaxf(fabsf((float)wu), fabsf((float)s)));
     if (lane == 0) wmu[(size_t)c * BR + i] = (float)s;
   }
   fro = wave_sum(fro);
@@ -220,9 +254,9 @@ __device__ inline _Float16 to_half(float v) {
 __global__ void __launch_bounds__(256)
 k_bound_pack(const float* __restrict__ Wd, const float* __restrict__ wmu,
              const float2* __restrict__ norms, const double* __restrict__ cst, int C, int Cpad,
-             int D, const int* __restrict__ maxbits, _Float16* __restrict__ Wf,
-             float2* __restrict__ cb) {
-  const float S = bound_scale(maxbits);
+             int D, const int* __restrict__ maxbits, const float* __restrict__ unit,
+             _Float16* __restrict__ Wf, float2* __restrict__ cb) {
+  const float S = bound_scale(maxbits), iu = 1.0f / unit[0];
   const int rb = blockIdx.x;  // component pair
   for (int e = threadIdx.x; e < 2 * 4 * 64; e += 256) {
     const int blk = e >> 8, ks = (e >> 6) & 3, l = e & 63;
@@ -235,7 +269,7 @@ k_bound_pack(const float* __restrict__ Wd, const float* __restrict__ wmu,
       float w = 0.0f;
       if (ok) {
         if (k < D) {
-          w = S * Wd[((size_t)c * BR + i) * 64 + k];
+          w = S * (iu * Wd[((size_t)c * BR + i) * 64 + k]);
         } else if (k <= D + 1) {
           const float m = -S * wmu[(size_t)c * BR + i];
           const float hi = (float)to_half(m);
@@ -271,8 +305,8 @@ __global__ void k_linv_quads(const double* __restrict__ linv, int C, int D,
 }
 
 // ------------------------------------------------------------------ the bound
-// Scaled quantities (S: bound_scale; t: the frame's power of two): x^ = fp16(t
-// x'), y^ = S t W (x' - mu') + d with ||d|| <= e_c g, g = ||t x' - x^|| +
+// Scaled quantities (S: bound_scale; t: the frame's power of two; x', mu' and W in
+// the units of k_bound_scale): x^ = fp16(t x'), y^ = S t W (x' - mu') + d with ||d|| <= e_c g, g = ||t x' - x^|| +
 // 2^-11 ||x^|| (rounding of the frame, of W_c; the FP32 sums and the split
 // mean are inside the rounded-up constants).  A component can reach the
 // threshold thr only if
@@ -284,17 +318,19 @@ __global__ void k_linv_quads(const double* __restrict__ linv, int C, int D,
 // 16 lanes per frame, four columns each.
 __global__ void __launch_bounds__(256)
 k_bound_frames(const float* __restrict__ X, int64_t F, int D, const float* __restrict__ shift,
-               const int* __restrict__ Fdev, _Float16* __restrict__ xh, float2* __restrict__ tg) {
+               const float* __restrict__ unit, const int* __restrict__ Fdev,
+               _Float16* __restrict__ xh, float2* __restrict__ tg) {
   if (Fdev && (int64_t)Fdev[0] < F) F = Fdev[0];
   const int l16 = threadIdx.x & 15;
   const int64_t g = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
   if (g >= F) return;  // uniform over the frame's 16 lanes
   float v[4], mx = 1.0f;
+  const float u0 = unit[0];
   bool fin = true;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const int k = 4 * l16 + e;
-    v[e] = k < D ? X[g * D + k] - shift[k] : 0.0f;
+    v[e] = k < D ? u0 * (X[g * D + k] - shift[k]) : 0.0f;
     fin = fin && isfinite(v[e]);
     mx = fmaxf(mx, fabsf(v[e]));
   }
@@ -1061,10 +1097,12 @@ void launch_bound_prepare(ivx_ctx* ctx, bool cov_changed, hipStream_t s) {
     k_bound_dirs<<<C, 256, dirs_lds(D), s>>>(ctx->linv, ctx->cst, D, ctx->Wd);
     k_linv_quads<<<2048, 256, 0, s>>>(ctx->linv, C, D, ctx->lquad);
   }
-  k_bound_scale<<<(C + 3) / 4, 256, 0, s>>>(ctx->Wd, ctx->mu, ctx->cst, ctx->shift, C, D, ctx->wmu,
-                                            ctx->bnorm, ctx->bmax);
+  k_bound_spread<<<(C + 3) / 4, 256, 0, s>>>(ctx->w, ctx->mu, ctx->cov, ctx->cst, ctx->shift, C, D,
+                                             ctx->bspread);
+  k_bound_scale<<<(C + 3) / 4, 256, 0, s>>>(ctx->Wd, ctx->mu, ctx->cst, ctx->shift, ctx->bspread, C,
+                                            D, ctx->wmu, ctx->bnorm, ctx->bmax, ctx->bunit);
   k_bound_pack<<<ctx->Cpad / 2, 256, 0, s>>>(ctx->Wd, ctx->wmu, ctx->bnorm, ctx->cst, C, ctx->Cpad,
-                                             D, ctx->bmax, ctx->Wf, ctx->cb);
+                                             D, ctx->bmax, ctx->bunit, ctx->Wf, ctx->cb);
 }
 
 void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
@@ -1097,7 +1135,7 @@ void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipS
   const unsigned nq = (unsigned)std::min<int64_t>((F + 31) / 32, 2 * (int64_t)ctx->ncu);
   const unsigned ne = (unsigned)std::min<int64_t>((F + 63) / 64, 8 * (int64_t)ctx->ncu);
   ProfScope ps(ctx, PK_FRAME_SELECT, s);
-  k_bound_frames<<<n16, 256, 0, s>>>(X, F, ctx->D, ctx->shift, Fdev, xh, tg);
+  k_bound_frames<<<n16, 256, 0, s>>>(X, F, ctx->D, ctx->shift, ctx->bunit, Fdev, xh, tg);
   const bool v4 = ctx->D % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
   // the sweeps over as many frames as their sums have room for, in equal parts;
   // without room for sums, all frames at once

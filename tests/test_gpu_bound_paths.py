@@ -1,0 +1,68 @@
+"""The bound that preselects components in large batches, away from the workload's
+models: against the dense kernel (an explicitly chosen launch shape), whose
+candidate lists it has to leave bit for bit, and in its time, which shows how
+many frames it had to hand on."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from _gpu_helpers import dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _frames(wl, F, seed):
+    """F frames drawn from the workload's own, with noise; more than the score buffer holds."""
+    rng = np.random.default_rng(seed)
+    assert 4 * F * ((wl.shape.C + 255) // 256 * 256) > 64 << 20
+    X = wl.X[rng.integers(0, wl.F, F)].astype(np.float64)
+    return X + 0.1 * rng.standard_normal(X.shape)
+
+
+def _context(w, mu, cov, F):
+    from paper_1906_08556_amd import ivx
+    ctx = ivx.Context(mu.shape[0], mu.shape[1], 2, 1, F)
+    ctx.set_ubm(dev(w), dev(mu), dev(cov))
+    return ctx
+
+
+def _run(ctx, X, prec, ncb, timed=False, check=True):
+    """Posterior lists with frame_ncb = ncb (8: the default route, 4: dense); least of 5 times."""
+    F = X.shape[0]
+    pi = torch.full((F, 16), -7, dtype=torch.int32, device="cuda")
+    pv = torch.full((F, 16), -7.0, device="cuda")
+    ll = torch.full((F,), -7.0, dtype=torch.float64, device="cuda")
+    ctx.tuning_set(frame_ncb=ncb, frame_ncb_bf16=ncb)
+    ms = []
+    for _ in range(6 if timed else 1):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        ctx.ubm_posteriors(X, post_idx=pi, post_val=pv, frame_ll=ll, prec=prec)
+        b.record()
+        torch.cuda.synchronize()
+        ms.append(a.elapsed_time(b))
+    if check:
+        ctx.sync_status()
+    return [t.cpu().numpy() for t in (pi, pv, ll)], min(ms)
+
+
+def _same(a, b):
+    for p, q in zip(a, b):
+        np.testing.assert_array_equal(p, q)
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -8, 2.0 ** -4, 2.0 ** 9])
+def test_bound_does_not_depend_on_the_scale_of_the_features(scale):
+    """Scaled by a power of two every product of the bound is the same; the time
+    is that of the unscaled model (factor 1.5: other work of the call is there
+    too, and a frame handed on costs six times one that is not)."""
+    wl = synth.make(2, R=4, U=20, lengths="uniform:1000:1000")
+    X = _frames(wl, 60000, 1).astype(np.float32)
+    plain = _context(wl.w, wl.mu, wl.cov, len(X))
+    _, t0 = _run(plain, dev(X), 0, 8, timed=True)
+    ctx = _context(wl.w, scale * wl.mu, scale ** 2 * wl.cov, len(X))
+    Xs = dev((scale * X).astype(np.float32))
+    got, t1 = _run(ctx, Xs, 0, 8, timed=True)
+    _same(got, _run(ctx, Xs, 0, 4)[0])
+    assert t1 <= 1.5 * t0, (t1, t0)
