@@ -58,6 +58,7 @@ constexpr int CL = 8;             // and sweep 2
 constexpr int SL = 32;            // listed components per lane-half and frame
 constexpr int kReplay = 1 << 16;    // flag bits above the candidate count
 constexpr int kFallback = 1 << 20;
+constexpr float kRelErr = 4e-6f;    // relative part of the allowance for FP32 scores
 constexpr float kFlush = 6.103515625e-5f;  // 2^-14, smallest normal FP16
 
 // ------------------------------------------------------------- preparation
@@ -545,7 +546,7 @@ k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
       const int bc = flag[g];
       const float M = Mf[g];
       // 3 nats for the FP32 errors of M, of the dense scores and of the test
-      const float thr = M - margin - 3.0f - 4e-6f * fabsf(M);
+      const float thr = M - margin - 3.0f - kRelErr * fabsf(M);
       bool good = fw + 32 * fb + l32 < F && bc >= 0 && q.x > 0.0f && isfinite(M);
       float eta = 1.0f;
       if (good) {
@@ -770,6 +771,8 @@ __device__ inline float unordered(int i) { return __int_as_float(i >= 0 ? i : i 
 // pairs of the component (rows 32..63 over all columns, rows 0..31 over
 // columns 0..31: 46 MFMAs).  First pass (score null): the frame's M.  Second
 // pass: the pair's score, and the frame's maximum as an ordered integer.
+// mu_c is taken in two FP32 parts: rounded to one, features far from the origin
+// (1e6 at unit deviations) would move a score by hundreds of nats.
 // A wave takes a contiguous range and loads the rows of the next run while it
 // scores this one; the ranges fill the device once (2 workgroups per CU).  4 M
 // frames, 20 M pairs: 0.9 ms on average for the two passes, near the FP32 MFMA
@@ -790,7 +793,7 @@ k_bound_quad(const float* __restrict__ X, int D, const int* __restrict__ coff, i
   if (e0 >= b1) return;
   int cur = -1;
   float4 a1[8], a0[4];  // rows l32 + 32 and l32, columns 4 (2 s + h) .. + 3
-  __shared__ float4 ms[4][16];  // mu_c of the wave
+  __shared__ float4 ms[4][2][16];  // mu_c of the wave, high and low parts
   const int wave = threadIdx.x >> 6;
   float cc = 0.0f;
   const float4 z4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -831,16 +834,19 @@ k_bound_quad(const float* __restrict__ X, int D, const int* __restrict__ coff, i
         for (int s = 0; s < 8; ++s) a1[s] = Lq[(2 * s + h) * 64 + 32];
 #pragma unroll
         for (int s = 0; s < 4; ++s) a0[s] = Lq[(2 * s + h) * 64];
-        reinterpret_cast<float*>(ms[wave])[lane] = (float)mu[(size_t)c * D + min(lane, D - 1)];
+        const double m = mu[(size_t)c * D + min(lane, D - 1)];
+        float* mw = reinterpret_cast<float*>(ms[wave]) + lane;
+        mw[0] = (float)m;
+        mw[64] = (float)(m - (double)(float)m);
         __builtin_amdgcn_wave_barrier();
         cc = (float)cst[c];
       }
       float4 d[8];
 #pragma unroll
-      for (int s = 0; s < 8; ++s)
-        {
-        const float4 m = ms[wave][2 * s + h];
-        d[s] = make_float4(x[s].x - m.x, x[s].y - m.y, x[s].z - m.z, x[s].w - m.w);
+      for (int s = 0; s < 8; ++s) {
+        const float4 m = ms[wave][0][2 * s + h], l = ms[wave][1][2 * s + h];
+        d[s] = make_float4((x[s].x - m.x) - l.x, (x[s].y - m.y) - l.y, (x[s].z - m.z) - l.z,
+                           (x[s].w - m.w) - l.w);
       }
       floatx16 y1 = floatx16{0}, y0 = floatx16{0};
 #pragma unroll
@@ -884,8 +890,11 @@ __device__ inline void append_cand(int2* cand, int* flag, int g, int c, float v)
 
 // Which pairs are candidates is the dense kernel's decision, taken from its
 // own scores; those differ from the FP32 scores here by less than half of
-// `err` nats.  A pair further than err inside or outside the margin is decided
-// either way; frames with a pair closer than that are marked for the replay.
+// `err` nats (and a few parts in 10^6 of their size).  A pair further than that
+// inside or outside the margin is decided either way; frames with a pair closer
+// than that are marked for the replay.
+__device__ inline float pair_err(float err, float M) { return err + kRelErr * fabsf(M); }
+
 __global__ void __launch_bounds__(256)
 k_bound_mark(const int* __restrict__ coff, int C, const int2* __restrict__ ent, int64_t cap,
              const float* __restrict__ score, const int* __restrict__ cMi, float margin, float err,
@@ -894,8 +903,8 @@ k_bound_mark(const int* __restrict__ coff, int C, const int2* __restrict__ ent, 
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * 256) {
     const int g = ent[e].x;
-    const float d = score[e] - (unordered(cMi[g]) - margin);
-    if (fabsf(d) <= err) atomicOr(flag + g, kReplay);
+    const float M = unordered(cMi[g]), d = score[e] - (M - margin);
+    if (fabsf(d) <= pair_err(err, M)) atomicOr(flag + g, kReplay);
   }
 }
 
@@ -919,8 +928,8 @@ k_bound_append(const int* __restrict__ coff, int C, const int2* __restrict__ ent
       const int64_t e = e0 + i + threadIdx.x;
       if (e >= total) break;
       const int2 p = ent[e];
-      const float s = score[e];
-      if (!(s >= unordered(cMi[p.x]) - margin - err)) continue;
+      const float s = score[e], M = unordered(cMi[p.x]);
+      if (!(s >= M - margin - pair_err(err, M))) continue;
       const int f = flag[p.x];
       if (f >= kFallback) continue;
       if (f & kReplay)

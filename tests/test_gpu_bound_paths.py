@@ -66,3 +66,14 @@ def test_bound_does_not_depend_on_the_scale_of_the_features(scale):
     got, t1 = _run(ctx, Xs, 0, 8, timed=True)
     _same(got, _run(ctx, Xs, 0, 4)[0])
     assert t1 <= 1.5 * t0, (t1, t0)
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("offset", [-2.0 ** 13, 2.0 ** 20])
+def test_bound_with_features_far_from_the_origin(offset, prec):
+    """FP32 features at an offset are 2^-11 or 2^-4 apart, but exact inputs: the
+    lists are those of the dense kernel, which takes them from their mean."""
+    wl = synth.make(2, R=4, U=20, lengths="uniform:1000:1000")
+    X = dev((_frames(wl, 30000, 2) + offset).astype(np.float32))
+    ctx = _context(wl.w, wl.mu + offset, wl.cov, len(X))
+    _same(_run(ctx, X, prec, 8)[0], _run(ctx, X, prec, 4)[0])
