@@ -283,7 +283,8 @@ k_bound_pack(const float* __restrict__ Wd, const float* __restrict__ wmu,
   }
   if (threadIdx.x < 2) {
     const int c = 2 * rb + threadIdx.x;
-    float2 o = make_float2(-1e30f, 0.0f);
+    // rejected and padding components: never the best, never listed
+    float2 o = make_float2(-INFINITY, 0.0f);
     if (c < C && isfinite(cst[c])) {
       const float e = S * (1.001f * norms[c].x + 0.0009765625f * norms[c].y) + 8.0f;
       o = make_float2((float)(2.0 * (double)S * (double)S * cst[c]), e * e);

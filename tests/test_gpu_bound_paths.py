@@ -77,3 +77,20 @@ def test_bound_with_features_far_from_the_origin(offset, prec):
     X = dev((_frames(wl, 30000, 2) + offset).astype(np.float32))
     ctx = _context(wl.w, wl.mu + offset, wl.cov, len(X))
     _same(_run(ctx, X, prec, 8)[0], _run(ctx, X, prec, 4)[0])
+
+
+def test_padding_components_are_never_taken():
+    """A model so wide that the scaled constants of its components (-2 S^2 cst_c,
+    about 1e33) pass any finite constant of a padding component; every frame
+    is within the margin of all of them and goes to the dense kernel."""
+    C, D, F, wide = 700, 33, 30000, 2.0 ** 108
+    rng = np.random.default_rng(3)
+    w = np.full(C, 1.0 / C)
+    mu = wide * rng.standard_normal((C, D))
+    mu -= mu.mean(0)
+    cov = np.broadcast_to(wide ** 2 * np.eye(D), (C, D, D)).copy()
+    X = dev((1e3 * rng.standard_normal((F, D))).astype(np.float32))
+    ctx = _context(w, mu, cov, F)
+    a, _ = _run(ctx, X, 0, 8, check=False)
+    assert a[0].max() < C
+    _same(a, _run(ctx, X, 0, 4, check=False)[0])
