@@ -352,8 +352,10 @@ bool bound_set_attributes(const ivx_ctx* ctx);
 void launch_bound_prepare(ivx_ctx* ctx, bool cov_changed, hipStream_t s);
 // Candidate lists as the dense kernel leaves them; the frames that only the
 // dense kernel can do are listed in *fb_list, their number in *fb_count (device).
+// *rest (device): F where the bound excludes too few components of a sample of the
+// frames and leaves all to the dense kernel (*fb_count is 0 then), else 0.
 void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
-                         const int* Fdev, int** fb_count, int** fb_list);
+                         const int* Fdev, int** fb_count, int** fb_list, int** rest);
 
 // ---- k_stats.hip
 // Frame -> utterance map of the batch in ctx->umap (offsets checked; bad

@@ -17,6 +17,10 @@
 // component is dropped only when its score is certainly more than the margin
 // below the frame's best.  The steps, per batch:
 //
+//   k_sample_sums / k_sample_count
+//                   the bound of a sample of the frames: whether it excludes
+//                   enough of their components to be worth the sweeps; if not,
+//                   the steps below get no frames and the dense kernel all
 //   k_bound_best    sweep 1 over all components finds the frame's best bound
 //                   (16 rows) and keeps the sums of all; the best component is
 //                   scored exactly (FP32 L^-1): M, a lower limit of the frame's
@@ -58,6 +62,7 @@ constexpr int CL = 8;             // and sweep 2
 constexpr int SL = 32;            // listed components per lane-half and frame
 constexpr int kReplay = 1 << 16;    // flag bits above the candidate count
 constexpr int kFallback = 1 << 20;
+constexpr int kListed = 14;       // listed pairs per frame that the entry array holds
 constexpr float kRelErr = 4e-6f;    // relative part of the allowance for FP32 scores
 constexpr float kFlush = 6.103515625e-5f;  // 2^-14, smallest normal FP16
 
@@ -365,6 +370,180 @@ k_bound_frames(const float* __restrict__ X, int64_t F, int D, const float* __res
                         fmaxf(1.01f * sqrtf(rho) + 0.000512f * sqrtf(nx), 0.015625f * t));
 }
 
+// The test of a frame, in nats: a component can reach thr = M - margin only if
+// v <= k1 u + k2 e - k3 with (u, e) its constants in cb and v its sum times rn.
+struct BoundTest {
+  float k1, k2, k3, rn;
+  bool good;  // false: outside the bound's range, nothing passes
+};
+__device__ inline BoundTest bound_test(float2 q, float S, float M, float margin, bool ok,
+                                       const float2* __restrict__ cb, int bc) {
+  BoundTest b;
+  const float S2x2 = 2.0f * S * S;
+  // 3 nats for the FP32 errors of M, of the dense scores and of the test
+  const float thr = M - margin - 3.0f - kRelErr * fabsf(M);
+  b.good = ok && bc >= 0 && q.x > 0.0f && isfinite(M);
+  float eta = 1.0f;
+  if (b.good) {
+    const float2 cv = cb[bc];
+    const float T = q.x * (cv.x - S2x2 * thr);
+    eta = fminf(fmaxf(sqrtf(cv.y / T) * q.y, 0.0009765625f), 8.0f);
+    if (!(eta > 0.0f)) eta = 1.0f;
+  }
+  b.rn = 1.0f / (S2x2 * q.x);
+  b.k1 = (1.0f + eta) / S2x2;
+  b.k2 = (1.0f + 1.0f / eta) * q.y * q.y * b.rn;
+  b.k3 = (1.0f + eta) * thr;
+  b.good = b.good && isfinite(b.k1) && isfinite(b.k2) && isfinite(b.k3) && isfinite(b.rn);
+  if (!b.good) {
+    b.k1 = b.k2 = 0.0f;
+    b.k3 = INFINITY;
+  }
+  return b;
+}
+__device__ inline float bound_limit(const BoundTest& b, float2 cv) {
+  return fmaf(b.k1, cv.x, fmaf(b.k2, cv.y, -b.k3));
+}
+
+// ------------------------------------------------------------------ the sample
+// How many components the bound leaves depends on the model's covariances and on
+// the frames: with 32 rows it sees little of a well-conditioned covariance (600
+// degrees of freedom instead of the workload's D + 5: 1800 of 2048 components
+// pass, every list overflows).  So 32 to 128 frames spread over the batch take
+// the test with all 32 rows first (19 us at C = 2048; where the bound
+// fails, the sweeps would waste 1.5 ms per 131,072 frames).
+constexpr int kSample = 128;
+constexpr int SP = 4;  // component pairs per workgroup of k_sample_sums
+// Costs by that of one dense tile of 128 frames per CU (2.3 ms in FP32 and 1.0 in
+// BF16 at C = 2048, D = 60, proportional to K): the bound's sweeps over F frames b0 +
+// b1 F, dearer by 0.4 of the share that it hands on; further dense rounds of two
+// tiles per CU h2; a frame by the split scores 1 / 20000.  (C = 2048, D = 60, FP32 /
+// BF16: bound 0.67 / 0.70 ms for 36,000 frames, 2.0 / 1.95 for 262,144; dense 2.5 /
+// 1.0 ms for 32,768, 4.2 / 1.4 for 65,536.)
+struct SampleRule {
+  float b0, b1, h2;
+  int round, fs;  // frames of a tile per CU, frames of the score buffer
+};
+__device__ inline bool bound_pays(const SampleRule& r, float F, float p) {
+  auto dense = [&](float n) { return n <= r.round ? 1.0f : r.h2 * ceilf(n / (2.0f * r.round)); };
+  const float n = p * F;
+  return (r.b0 + r.b1 * F) * (1.0f + 0.4f * p) + (n <= r.fs ? n * 5e-5f : dense(n)) < dense(F);
+}
+__device__ inline int64_t sample_frame(int64_t F, int i, int n) { return F * i / n; }
+
+// sv [ns][Cpad]: the sums over 16 and over 32 rows in nats; a wave per 32 frames
+__global__ void __launch_bounds__(256)
+k_sample_sums(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int64_t F,
+              const _Float16* __restrict__ Wf, const int* __restrict__ maxbits, int Cpad, int ns,
+              float2* __restrict__ sv, int* __restrict__ dec, const int* __restrict__ Fdev) {
+  if (Fdev && (int64_t)Fdev[0] < F) F = Fdev[0];
+  if (blockIdx.x == 0 && threadIdx.x < 5) dec[threadIdx.x] = 0;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, h = lane >> 5, l32 = lane & 31;
+  if (F <= 0 || 32 * wave >= ns) return;
+  const int64_t g = sample_frame(F, 32 * wave + l32, ns);
+  const float S = bound_scale(maxbits);
+  const float rn = 1.0f / (2.0f * S * S * tg[g].x);
+  half8 xf[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks)
+    xf[ks] = *reinterpret_cast<const half8*>(xh + g * BK + 16 * ks + 8 * h);
+  const half8* W8 = reinterpret_cast<const half8*>(Wf) + (size_t)blockIdx.x * SP * 512 + lane;
+  float2* out = sv + (size_t)(32 * wave + l32) * Cpad + (size_t)blockIdx.x * SP * 2 + h;
+#pragma unroll 2
+  for (int i = 0; i < SP; ++i) {
+    float sq[2] = {0.0f, 0.0f};
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk) {
+      floatx16 ac = floatx16{0};
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+        ac = __builtin_amdgcn_mfma_f32_32x32x16_f16(W8[i * 512 + blk * 256 + ks * 64], xf[ks], ac,
+                                                    0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sq[blk] = fmaf(ac[r], ac[r], sq[blk]);
+    }
+    out[2 * i] = make_float2(sq[0] * rn, (sq[0] + sq[1]) * rn);
+  }
+}
+
+// One wave per sampled frame: its best component (on 16 rows, as in sweep 1), that
+// one's exact score, the components that pass.  The last one decides: dec[0] frames for the bound,
+// dec[1] for the dense kernel (all or none); dec[2..4] counters.
+__global__ void __launch_bounds__(64)
+k_sample_count(const float* __restrict__ X, int64_t F, int D, const float2* __restrict__ tg,
+               const float2* __restrict__ cb, const int* __restrict__ maxbits, int Cpad,
+               float margin, const double* __restrict__ mu, const float* __restrict__ lquad,
+               const double* __restrict__ cst, const float2* __restrict__ sv, SampleRule rule,
+               int* __restrict__ dec, const int* __restrict__ Fdev) {
+  __shared__ float ds[64];
+  if (Fdev && (int64_t)Fdev[0] < F) F = Fdev[0];
+  const int lane = threadIdx.x, ns = gridDim.x;
+  const float S = bound_scale(maxbits), r2 = 0.5f / (S * S);
+  bool bad = false;
+  int cnt = 0;
+  if (F > 0) {
+    const int64_t g = sample_frame(F, blockIdx.x, ns);
+    const float2* v = sv + (size_t)blockIdx.x * Cpad;
+    float bv = INFINITY;
+    int bc = -1;
+#pragma unroll 4
+    for (int c = lane; c < Cpad; c += 64) {
+      const float k = v[c].x - cb[c].x * r2;
+      bc = k < bv ? c : bc;
+      bv = fminf(k, bv);
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      const float ov = __shfl_xor(bv, o);
+      const int oc = __shfl_xor(bc, o);
+      if (ov < bv || (ov == bv && oc < bc)) bc = oc;
+      bv = fminf(bv, ov);
+    }
+    bc = __builtin_amdgcn_readfirstlane(bc);
+    float M = -INFINITY;
+    if (bc >= 0) {  // uniform; one wave
+      ds[lane] = lane < D ? (float)((double)X[g * D + lane] - mu[(size_t)bc * D + lane]) : 0.0f;
+      __syncthreads();
+      const float4* Lq = reinterpret_cast<const float4*>(lquad) + (size_t)bc * 1024 + lane;
+      float y = 0.0f;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const float4 l = Lq[q * 64];
+        y = fmaf(l.x, ds[4 * q], y);
+        y = fmaf(l.y, ds[4 * q + 1], y);
+        y = fmaf(l.z, ds[4 * q + 2], y);
+        y = fmaf(l.w, ds[4 * q + 3], y);
+      }
+      float q = y * y;
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) q += __shfl_xor(q, o);
+      M = (float)cst[bc] - 0.5f * q;
+    }
+    const BoundTest b = bound_test(tg[g], S, M, margin, true, cb, bc);
+    // c = lane + 64 i: the parity of the lane is the component's
+#pragma unroll 4
+    for (int c = lane; c < Cpad; c += 64) cnt += v[c].y <= bound_limit(b, cb[c]) ? 1 : 0;
+#pragma unroll
+    for (int o = 32; o >= 2; o >>= 1) cnt += __shfl_xor(cnt, o);
+    const int other = __shfl_xor(cnt, 1);
+    bad = !b.good || cnt > SL || other > SL;
+    cnt += other;
+  }
+  if (lane != 0) return;
+  if (bad)
+    atomicAdd(dec + 2, 1);
+  else
+    atomicAdd(dec + 3, cnt);
+  __threadfence();
+  if (atomicAdd(dec + 4, 1) != ns - 1) return;
+  __threadfence();
+  const int nbad = atomicAdd(dec + 2, 0), sum = atomicAdd(dec + 3, 0);
+  // lists of more than kListed pairs per frame do not fit the entry array
+  const bool use = bound_pays(rule, (float)F, (float)nbad / ns) && sum <= (kListed - 2) * ns;
+  dec[0] = use ? (int)F : 0;
+  dec[1] = use ? 0 : (int)F;
+}
+
 // Both sweeps: one persistent workgroup of 8 waves per 256 FB frames, FB blocks
 // of 32 frames per wave (lane l: frame l % 32 of each block, component parity
 // l / 32).  Sweep 1 is bound by the matrix cores (per 32 x 32 block 4 MFMAs, 128
@@ -534,7 +713,7 @@ k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
   for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
     const int64_t fw = f0 + tile * FT + wave * 32 * FB;
     half8 xf[FB][4];
-    float k1[FB], k2[FB], k3[FB], rn[FB];  // in nats: the test is k1 u + k2 e - k3 >= v
+    BoundTest bt[FB];
     int cnt[FB];
 #pragma unroll
     for (int fb = 0; fb < FB; ++fb) {
@@ -542,30 +721,9 @@ k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks)
         xf[fb][ks] = *reinterpret_cast<const half8*>(xh + g * BK + 16 * ks + 8 * h);
-      const float2 q = tg[g];
-      const float S = bound_scale(maxbits), S2x2 = 2.0f * S * S;
-      const int bc = flag[g];
-      const float M = Mf[g];
-      // 3 nats for the FP32 errors of M, of the dense scores and of the test
-      const float thr = M - margin - 3.0f - kRelErr * fabsf(M);
-      bool good = fw + 32 * fb + l32 < F && bc >= 0 && q.x > 0.0f && isfinite(M);
-      float eta = 1.0f;
-      if (good) {
-        const float2 cv = cb[bc];
-        const float T = q.x * (cv.x - S2x2 * thr);
-        eta = fminf(fmaxf(sqrtf(cv.y / T) * q.y, 0.0009765625f), 8.0f);
-        if (!(eta > 0.0f)) eta = 1.0f;
-      }
-      rn[fb] = 1.0f / (S2x2 * q.x);
-      k1[fb] = (1.0f + eta) / S2x2;
-      k2[fb] = (1.0f + 1.0f / eta) * q.y * q.y * rn[fb];
-      k3[fb] = (1.0f + eta) * thr;
-      good = good && isfinite(k1[fb]) && isfinite(k2[fb]) && isfinite(k3[fb]) && isfinite(rn[fb]);
-      if (!good) {
-        k1[fb] = k2[fb] = 0.0f;
-        k3[fb] = INFINITY;
-      }
-      cnt[fb] = good ? 0 : SL + 1;
+      bt[fb] = bound_test(tg[g], bound_scale(maxbits), Mf[g], margin, fw + 32 * fb + l32 < F, cb,
+                          flag[g]);
+      cnt[fb] = bt[fb].good ? 0 : SL + 1;
     }
     // stage ch in buffer b: the operands of NP pairs (512 entries per copy: two
     // pairs' second blocks, or one pair) and their constants
@@ -609,7 +767,7 @@ k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
         bool pass[FB], any = false;
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb) {
-          t[fb] = fmaf(k1[fb], cv.x, fmaf(k2[fb], cv.y, -k3[fb]));
+          t[fb] = bound_limit(bt[fb], cv);
           if constexpr (KEPT) {
             v[fb] = cut_value(w[i / CH][fb][i % CH >> 1], i & 1);
           } else {
@@ -620,7 +778,7 @@ k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
             float sq = ac[0] * ac[0];
 #pragma unroll
             for (int r = 1; r < 16; ++r) sq = fmaf(ac[r], ac[r], sq);
-            v[fb] = sq * rn[fb];
+            v[fb] = sq * bt[fb].rn;
           }
           pass[fb] = v[fb] <= t[fb];
           any = any || pass[fb];
@@ -639,7 +797,7 @@ k_bound_list(const _Float16* __restrict__ xh, const float2* __restrict__ tg, int
           float sq = ac[0] * ac[0];
 #pragma unroll
           for (int r = 1; r < 16; ++r) sq = fmaf(ac[r], ac[r], sq);
-          if (pass[fb] && fmaf(sq, rn[fb], v[fb]) <= t[fb]) {
+          if (pass[fb] && fmaf(sq, bt[fb].rn, v[fb]) <= t[fb]) {
             const int64_t g = fw + 32 * fb + l32;
             if (cnt[fb] < SL) surv[g * 64 + h * SL + cnt[fb]] = (uint16_t)(2 * (ch * NP + i) + h);
             ++cnt[fb];
@@ -1116,7 +1274,7 @@ void launch_bound_prepare(ivx_ctx* ctx, bool cov_changed, hipStream_t s) {
 }
 
 void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
-                         const int* Fdev, int** fb_count, int** fb_list) {
+                         const int* Fdev, int** fb_count, int** fb_list, int** rest) {
   const bool bf = prec == IVX_BF16;
   const float margin = bf ? ctx->margin_bf16 : ctx->margin;
   // the FP32 dense scores are off by up to 0.4 nats on the workload, the BF16
@@ -1125,8 +1283,9 @@ void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipS
   // workspace, all in arrays that the rescoring writes later: the FP16 frames
   // in ent, replaced there by the sorted pairs of sweep 2 (at most 14 F); the
   // pairs of sweep 1 and (t^2, g) in lscore, replaced by the pairs' scores,
-  // two counters, the dense kernel's frames and the pairs to replay
-  const int64_t cap = 14 * F;
+  // two counters, the dense kernel's frames and the pairs to replay; the
+  // sample's decision behind them
+  const int64_t cap = kListed * F;
   _Float16* xh = reinterpret_cast<_Float16*>(ctx->ent);
   char* w8 = reinterpret_cast<char*>(ctx->lscore);
   int2* ent1 = reinterpret_cast<int2*>(w8);
@@ -1135,6 +1294,8 @@ void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipS
   int* cnts = reinterpret_cast<int*>(w8 + 56 * F);
   int* fb = cnts + 2;
   int* rep = fb + F;
+  int* dec = reinterpret_cast<int*>(w8 + 120 * F);  // 5 ints; rep ends at 116 F + 8
+  static_assert(56 + 4 + 4 * kListed <= 116, "workspace layout");
   static_assert(KP == 16 && sizeof(int2) * KP == 2 * BK, "workspace layout");
   uint16_t* surv = reinterpret_cast<uint16_t*>(ctx->cand);
   int* cMi = reinterpret_cast<int*>(ctx->cM);
@@ -1146,6 +1307,24 @@ void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipS
   const unsigned ne = (unsigned)std::min<int64_t>((F + 63) / 64, 8 * (int64_t)ctx->ncu);
   ProfScope ps(ctx, PK_FRAME_SELECT, s);
   k_bound_frames<<<n16, 256, 0, s>>>(X, F, ctx->D, ctx->shift, ctx->bunit, Fdev, xh, tg);
+  // the sample's sums, in the candidate or the score buffer (both written later)
+  const float k60 = 1891.0f / (float)ctx->K;
+  const SampleRule rule = {k60 * (bf ? 0.5f : 0.2f), k60 * (bf ? 5.5e-6f : 2.6e-6f),
+                           bf ? 1.5f : 1.85f, 128 * ctx->ncu, (int)scores_frames(ctx)};
+  const int64_t room = std::max<int64_t>(128 * F, (int64_t)ctx->scores_bytes);
+  float2* sv = 128 * F >= (int64_t)ctx->scores_bytes ? reinterpret_cast<float2*>(ctx->cand)
+                                                      : reinterpret_cast<float2*>(ctx->scores);
+  const int ns = (int)std::min<int64_t>(kSample, room / (8 * ctx->Cpad) / 32 * 32);
+  *rest = nullptr;
+  if (ns > 0) {
+    k_sample_sums<<<ctx->Cpad / (2 * SP), 256, 0, s>>>(xh, tg, F, ctx->Wf, ctx->bmax, ctx->Cpad, ns,
+                                                       sv, dec, Fdev);
+    k_sample_count<<<ns, 64, 0, s>>>(X, F, ctx->D, tg, ctx->cb, ctx->bmax, ctx->Cpad,
+                                     margin + err - 3.0f, ctx->mu, ctx->lquad, ctx->cst, sv,
+                                     rule, dec, Fdev);
+    Fdev = dec;
+    *rest = dec + 1;
+  }
   const bool v4 = ctx->D % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
   // the sweeps over as many frames as their sums have room for, in equal parts;
   // without room for sums, all frames at once

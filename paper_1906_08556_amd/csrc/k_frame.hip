@@ -769,7 +769,8 @@ void launch_frame_dense(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipSt
 //    components (k_scores.hip);
 //  * more, where the bound's conditions hold and its 32-bit list positions (64
 //    per frame) suffice: the bound (k_bound.hip), the frames it cannot serve
-//    as above, or by the dense kernel when they are too many;
+//    as above, or by the dense kernel when they are too many; all frames by the
+//    dense kernel where a sample of them shows that the bound excludes too little;
 //  * else the dense kernel.
 void launch_frame_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipStream_t s,
                          const int* Fdev) {
@@ -782,10 +783,11 @@ void launch_frame_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipS
     return;
   }
   if (!chosen && ctx->Wf && F < (int64_t(1) << 25)) {
-    int *fb_count, *fb_list;
-    launch_bound_select(ctx, X, F, prec, s, Fdev, &fb_count, &fb_list);
+    int *fb_count, *fb_list, *rest;
+    launch_bound_select(ctx, X, F, prec, s, Fdev, &fb_count, &fb_list, &rest);
     launch_scores_select(ctx, X, F, prec, s, fb_count, fb_list);
     launch_frame_dense(ctx, X, F, prec, s, fb_count, fb_list, fs);
+    if (rest) launch_frame_dense(ctx, X, F, prec, s, rest);
     return;
   }
   launch_frame_dense(ctx, X, F, prec, s, Fdev);
