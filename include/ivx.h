@@ -110,6 +110,11 @@ typedef struct {
 
 /* Creates a context on HIP device `device` and allocates all model storage
  * and workspace for `dims` (the only call besides ivx_set_* that allocates).
+ * The frame stage's share of it: about 530 bytes per frame of max_batch_frames
+ * (IVX_SEL_ALL), up to 64 MB of scores, and, where it preselects components (C >= 512,
+ * 32 <= D <= 62, batches beyond the score buffer, 16 Mi / C frames), 2 C bytes per
+ * frame up to 2 GB, but not more than an eighth of the free device memory: with
+ * less, or C > 8192, the call does without (and its preselection takes longer).
  * Returns IVX_EINVAL for bad dims, IVX_ENOMEM if allocation fails. */
 ivx_status ivx_create(const ivx_dims* dims, int device, ivx_ctx** out);
 
@@ -534,13 +539,14 @@ ivx_status ivx_stream_extract(ivx_stream* st, const float* X, ivx_frame_source s
  * of every threshold t among the scores and above them, joined by straight
  * segments, misses being targets below t and false alarms non-targets at or
  * above t.
- * Symmetric eigenproblems are solved on the GPU by a one-workgroup Jacobi
- * method in FP64.  Vectors are FP32 [n][dim] rows, matrices FP64 row-major,
+ * Symmetric eigenproblems are solved on the GPU by a cyclic Jacobi method in
+ * FP64.  Vectors are FP32 [n][dim] rows, matrices FP64 row-major,
  * all on the device unless stated. */
 typedef struct ivx_backend ivx_backend;
 
 /* Workspace for up to max_n vectors of dimension <= max_dim (2..512) and up
- * to max_classes classes.  IVX_ENOMEM if allocation fails. */
+ * to max_classes classes, and for the scores of all pairs of up to 4096 of them
+ * (64 MB at most).  IVX_ENOMEM if allocation fails. */
 ivx_status ivx_backend_create(int32_t max_dim, int64_t max_n, int32_t max_classes, int device,
                               ivx_backend** out);
 void ivx_backend_destroy(ivx_backend* be);

@@ -253,15 +253,20 @@ ivx_status ivx_create(const ivx_dims* dims, int device, ivx_ctx** out) {
   A(dalloc(&c->mvec, 4 * R));
   A(dalloc(&c->mstat, C));
   A(dalloc(&c->dev_err, 4));
-  if (c->Wf) {  // last: with less memory left than asked for, fewer frames per pass
-    c->sweep_frames = bound_sweep_frames(c->Cpad, (int64_t)F);
-    while (ok && c->sweep_frames > 4096 &&
-           dalloc(&c->sums16, (size_t)c->sweep_frames * c->Cpad) != hipSuccess) {
+  // last: the sums between the bound's sweeps, where batches are large enough for
+  // the bound and an eighth of the free memory holds them (without them sweep 2
+  // takes twice as long)
+  if (ok && c->Wf && (int64_t)F > scores_frames(c)) {
+    size_t free_bytes = 0, total_bytes = 0;
+    const int64_t n = bound_sweep_frames(c->Cpad, (int64_t)F);
+    if (n > 0 && hipMemGetInfo(&free_bytes, &total_bytes) == hipSuccess &&
+        sizeof(uint16_t) * (size_t)n * c->Cpad <= free_bytes / 8 &&
+        dalloc(&c->sums16, (size_t)n * c->Cpad) == hipSuccess) {
+      c->sweep_frames = n;
+    } else {
       (void)hipGetLastError();
       c->sums16 = nullptr;
-      c->sweep_frames = c->sweep_frames / 1024 * 512;
     }
-    if (!c->sums16) A(dalloc(&c->sums16, (size_t)c->sweep_frames * c->Cpad));
   }
   if (!ok) {
     ivx_destroy(c);

@@ -345,8 +345,9 @@ void launch_scores_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hip
 
 // ---- k_bound.hip
 bool bound_supported(int C, int D);
-// frames the sweeps take at a time: 2 GB of sums (524288 frames at C = 2048; the
-// device works on 262144), at least one block of frames per wave
+// frames the sweeps take at a time with kept sums: 2 GB of them (524288 frames at C =
+// 2048; the device works on 262144); 0 where that is less than a block of frames
+// per wave of the whole device (131072; C > 8192): nothing is kept
 int64_t bound_sweep_frames(int Cpad, int64_t maxF);
 bool bound_set_attributes(const ivx_ctx* ctx);
 void launch_bound_prepare(ivx_ctx* ctx, bool cov_changed, hipStream_t s);

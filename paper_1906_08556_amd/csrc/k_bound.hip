@@ -1238,14 +1238,14 @@ size_t dirs_lds(int D) { return sizeof(double) * ((size_t)D * D + 2 * (size_t)D 
 
 }  // namespace
 
+int64_t bound_sweep_frames(int Cpad, int64_t maxF) {
+  const int64_t n = (int64_t(1) << 30) / Cpad / 512 * 512;
+  return n < (int64_t(1) << 17) ? 0 : std::min<int64_t>(n, (maxF + 511) / 512 * 512);
+}
+
 // The bound needs D + 2 <= 64 columns and at least 32 dimensions for its rows,
 // 16-bit component ids, and enough components that sweeping them twice on
 // FP16 with 16 rows is cheaper than once in FP32 with (D + 1)(D + 2) / 2.
-int64_t bound_sweep_frames(int Cpad, int64_t maxF) {
-  const int64_t n = std::max<int64_t>(int64_t(1) << 17, (int64_t(1) << 30) / Cpad / 512 * 512);
-  return std::min<int64_t>(n, (maxF + 511) / 512 * 512);
-}
-
 bool bound_supported(int C, int D) { return D >= BR && D + 2 <= BK && C >= 512 && C <= 65536; }
 
 bool bound_set_attributes(const ivx_ctx* ctx) {
@@ -1327,7 +1327,7 @@ void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipS
   }
   const bool v4 = ctx->D % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
   // the sweeps over as many frames as their sums have room for, in equal parts;
-  // without room for sums, all frames at once
+  // without sums, all frames at once
   uint2v* sums = reinterpret_cast<uint2v*>(ctx->sums16);
   const int64_t parts = sums ? (F + ctx->sweep_frames - 1) / ctx->sweep_frames : 1;
   const int64_t step = ((F + parts - 1) / parts + 511) / 512 * 512;

@@ -120,3 +120,20 @@ def test_models_whose_components_the_bound_cannot_exclude(C, D, std, shift, prec
     want, t4 = _run(ctx, X, prec, 4, timed=True)
     _same(got, want)
     assert t <= 1.1 * t4, (t, t4)
+
+
+def test_memory_of_a_context_with_many_components():
+    """The sums between the sweeps take at most 2 GB, also where that holds fewer
+    frames than the device works on (8192 < C); 1 KB per frame for all else."""
+    from paper_1906_08556_amd import ivx
+
+    def used(F):
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        ctx = ivx.Context(16384, 32, 2, 1, F)
+        n = free - torch.cuda.mem_get_info()[0]
+        del ctx
+        return n
+
+    used(2000)  # the library's own first-time allocations
+    assert used(140000) - used(2000) <= (2 << 30) + (64 << 20) + 1024 * 140000
