@@ -137,3 +137,62 @@ def test_memory_of_a_context_with_many_components():
 
     used(2000)  # the library's own first-time allocations
     assert used(140000) - used(2000) <= (2 << 30) + (64 << 20) + 1024 * 140000
+
+
+@pytest.mark.parametrize("C,D,F,prec", [(512, 32, 33000, 0), (512, 40, 140000, 1), (701, 62, 22000, 0),
+                                        (701, 62, 22000, 1), (2048, 33, 9000, 0)])
+def test_bound_at_the_edges_of_its_range(C, D, F, prec):
+    """Fewest components and dimensions, most dimensions, padded components, rows that
+    are no whole float4: with lists that overflow (100 nearly equal components) and
+    frames outside the bound's range, the lists are the dense kernel's."""
+    from paper_1906_08556_amd import ivx
+    wl = synth.make(2, C=C, D=D, R=4, U=20, lengths="uniform:1000:1000")
+    X = _frames(wl, F, 6)
+    mu, cov = wl.mu.copy(), wl.cov.copy()
+    mu[-100:] = mu[-1] + 50.0 + 1e-3 * np.arange(100)[:, None]
+    cov[-100:] = cov[-1]
+    rng = np.random.default_rng(5)
+    X[100:140] = mu[-50] + rng.standard_normal((40, D)) @ np.linalg.cholesky(cov[-1]).T
+    X[200:210] *= 1e4
+    X[300] = 3e7
+    X[301, D - 1] = np.inf
+    X[F - 1, 0] = np.nan
+    X = dev(X.astype(np.float32))
+    ctx = _context(wl.w, mu, cov, F)
+    out = []
+    for ncb in (8, 4):
+        out.append(_run(ctx, X, prec, ncb, check=False)[0])
+        with pytest.raises(ivx.IvxError):
+            ctx.sync_status()
+    assert np.all(out[0][0][100:140] >= C - 100)
+    _same(*out)
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp32", "bf16"])
+def test_more_frames_handed_on_than_the_score_buffer_holds(prec):
+    """22,500 of 150,000 frames lie beyond the bound's range (2^21 units): the dense
+    kernel takes them through their list, and the others' lists are its own too."""
+    wl = synth.make(2, R=4, U=20, lengths="uniform:1000:1000")
+    X = _frames(wl, 150000, 7)
+    X[np.random.default_rng(8).permutation(len(X))[:22500]] *= 1e7
+    X = dev(X.astype(np.float32))
+    ctx = _context(wl.w, wl.mu, wl.cov, len(X))
+    _same(_run(ctx, X, prec, 8)[0], _run(ctx, X, prec, 4)[0])
+
+
+def test_bound_of_two_contexts_on_two_streams():
+    wl = synth.make(2, R=4, U=20, lengths="uniform:1000:1000")
+    X = [dev(_frames(wl, 30000, s).astype(np.float32)) for s in (9, 10)]
+    ctx = [_context(wl.w, wl.mu, wl.cov, 30000) for _ in X]
+    want = [_run(c, x, 0, 8)[0] for c, x in zip(ctx, X)]
+    streams = [torch.cuda.Stream() for _ in X]
+    for _ in range(5):
+        out = [(torch.full((30000, 16), -7, dtype=torch.int32, device="cuda"),
+                torch.full((30000, 16), -7.0, device="cuda"),
+                torch.full((30000,), -7.0, dtype=torch.float64, device="cuda")) for _ in X]
+        torch.cuda.synchronize()
+        for c, x, o, s in zip(ctx, X, out, streams):
+            c.ubm_posteriors(x, post_idx=o[0], post_val=o[1], frame_ll=o[2], stream=s)
+        torch.cuda.synchronize()
+        for o, w in zip(out, want):
+            _same([t.cpu().numpy() for t in o], w)
