@@ -182,8 +182,10 @@ ivx_status ivx_selector_set(ivx_ctx* ctx, const ivx_selector_dims* sd, const flo
     A(salloc(&S->dh2, B * H2));
     A(salloc(&S->loss_part, B));
     A(salloc(&S->colpart, 32 * std::max<int64_t>(C, std::max(H1, H2))));
-    // eight splits of the largest weight gradient (dW3 at C = 2048, H2 = 512: 32 MB)
-    S->gws_elems = 8 * std::max<int64_t>(C * H2, H2 * H1);
+    // eight splits of the largest weight gradient (dW3 at C = 2048, H2 = 512: 32 MB);
+    // products of 512 tiles of 128 x 128 and more are not split, and the splits of
+    // fewer tiles never hold more than 1024 tiles' elements
+    S->gws_elems = std::min<int64_t>(8 * std::max<int64_t>(C * H2, H2 * H1), 2 * 512 * 128 * 128);
     A(salloc(&S->gws, S->gws_elems));
   }
   if (!ok) {

@@ -81,3 +81,24 @@ def test_selector_gradients_on_large_tiles():
            dz.T @ np.abs(cache[4]), dz.sum(0))
     for g, r, m in zip(synth.mlp_split(grad.cpu().numpy(), D, h1, h2, C), ref, mag):
         assert np.linalg.norm(g - r) <= 1e-5 * np.linalg.norm(m)
+
+
+def test_memory_of_a_wide_selector():
+    """Hidden layers of 4096: the partial products of the split weight gradients take
+    at most 64 MB beside the training batch's own arrays (16 frames here, the column
+    sums' 32 rows, 8 MB for allocation granules)."""
+    from paper_1906_08556_amd import ivx
+    C, D, H, B = 300, 20, 4096, 16
+    rng = np.random.default_rng(1)
+    params = dev((0.01 * rng.standard_normal(H * (D + 1) + H * (H + 1) + C * (H + 1))).astype(np.float32))
+    mean, std = dev(np.zeros(D, np.float32)), dev(np.ones(D, np.float32))
+    ctx = ivx.Context(C, D, 2, 1, 64)
+
+    def free(batch):
+        ctx.selector_set(params, mean, std, H1=H, H2=H, k=20, max_train_batch=batch)
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    free(0)
+    a = free(0)
+    assert a - free(B) <= (64 << 20) + 4 * (B * 8 * H + 32 * H) + (8 << 20)
