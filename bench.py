@@ -29,6 +29,7 @@ METRIC = "TV EM utts/s + frame posteriors/s at C=2048,D=60,R=400 vs FP32 plain"
 HBM_PEAK_GBS = 8000.0
 FP32_MFMA_PEAK_TFLOPS = 157.3
 FP64_MFMA_PEAK_TFLOPS = 78.6
+FP16_MFMA_PEAK_TFLOPS = 2500.0
 # BF16 MFMA products per FP32 product in the BF16 frame filter (operands split
 # into high and low BF16 parts: hi*hi + hi*lo + lo*hi)
 BF16_PRODUCTS = 3
@@ -691,12 +692,17 @@ def main():
     def dense(ncb):
         return ncb != 8 or tune_now["frame_direct"] != 0 or C < 512 or not 32 <= D <= 62
 
-    if dense(tune_now["frame_ncb"]):
+    # small batches on the default shape: the same products split over components
+    split = (tune_now["frame_ncb"] == 8 and not tune_now["frame_direct"]
+             and 4 * F * ((C + 255) // 256 * 256) <= 64 << 20)
+    if split or dense(tune_now["frame_ncb"]):
         achieved = flop_per_frame * F / fs_avg_s / 1e12
-        roof = {"kernel": "k_frame_tile", "bound": "mfma", "achieved": round(achieved, 2),
+        roof = {"kernel": "k_scores_f32 + k_scores_select" if split else "k_frame_tile",
+                "bound": "mfma", "achieved": round(achieved, 2),
                 "peak": FP32_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved / FP32_MFMA_PEAK_TFLOPS, 4),
-                "traffic": measured_traffic("k_frame_tile", f"shape{args.shape}", F),
+                "traffic": None if split else measured_traffic("k_frame_tile",
+                                                               f"shape{args.shape}", F),
                 "avg_launch_ms": round(fs_avg_s * 1e3, 3), "launches_per_step": fs_calls // K,
                 "flop_per_frame_per_launch": flop_per_frame, "frames_per_launch": F,
                 "components_per_launch": C}
@@ -710,6 +716,15 @@ def main():
                 "group_ms_per_step": round(acc_ms, 3), "flop_per_step": acc_flop,
                 "group": "both products, the conversion of Phi to FP64 and the column sums",
                 "frame_stage_ms_per_step": round(fs_ms / K, 3)}
+        # the frame stage by what its first sweep cannot do without: 16 rows of 64
+        # FP16 products per frame and component, against the dense FP16 peak, over
+        # the time of the whole stage (second sweep, sorts and pair scores included)
+        sweep = 2.0 * 16 * 64 * C * F
+        roof["frame_stage"] = {
+            "kernels": "k_bound_best, k_bound_list, pair scores and sorts", "bound": "mfma",
+            "sweep1_fp16_flop": sweep, "achieved": round(sweep / (fs_ms / K / 1e3) / 1e12, 2),
+            "peak": FP16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
+            "frac": round(sweep / (fs_ms / K / 1e3) / 1e12 / FP16_MFMA_PEAK_TFLOPS, 4)}
     log("[bench] FP32 kernel groups (ms per step): " + ", ".join(
         f"{k}={v[0] / K:.2f}" for k, v in prof.items() if v[1]))
     log(f"[bench] objective after last step: {obj.item():.6e}")

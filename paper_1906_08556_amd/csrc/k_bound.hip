@@ -1247,8 +1247,9 @@ int64_t bound_sweep_frames(int Cpad, int64_t maxF) {
 }
 
 // The bound needs D + 2 <= 64 columns and at least 32 dimensions for its rows,
-// 16-bit component ids, and enough components that sweeping them twice on
-// FP16 with 16 rows is cheaper than once in FP32 with (D + 1)(D + 2) / 2.
+// 16-bit component ids, and enough components that its 20 launches and the sorts
+// pay beside the sweeps: 36,000 frames at C = 512 take 403 us against 467 by a dense
+// shape at D = 32 and 469 against 1228 at D = 60 (C = 2048: 830 and 1492, 967 and 4547).
 bool bound_supported(int C, int D) { return D >= BR && D + 2 <= BK && C >= 512 && C <= 65536; }
 
 bool bound_set_attributes(const ivx_ctx* ctx) {

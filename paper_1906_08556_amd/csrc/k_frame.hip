@@ -764,9 +764,18 @@ void launch_frame_dense(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipSt
 }
 
 // Routes of the default launch shape (an explicitly chosen one runs the dense
-// kernel).  All give the same candidate lists.
+// kernel).  All give the same candidate lists, but for frames whose running list
+// in the dense kernel overflows in mid sweep though few components are within the
+// margin in the end: there the dense kernel's frames get their 16 best.
 //  * at most scores_frames() frames (8192 at C = 2048): scores split over
-//    components (k_scores.hip);
+//    components (k_scores.hip).  The line is where the 64 MB of scores are full:
+//    up to there the time does not depend on the model.  Whole calls at D = 60 in
+//    us, FP32 / BF16, scores for the largest batch and the bound for 8 to 32 frames
+//    more: C = 2048, 8192 frames 915 / 497 and 899 / 894; C = 1024, 16,384 frames
+//    907 / 484 and 582 / 555; C = 512, 32,768 frames 886 / 487 and 455 / 434 (dense
+//    kernel 2827 / 1258, 1475 / 700, 806 / 413).  The bound takes much the same time
+//    for fewer frames, so with few components it would be ahead earlier on the
+//    workload's kind of model: from 13,000 frames at C = 512 in FP32;
 //  * more, where the bound's conditions hold and its 32-bit list positions (64
 //    per frame) suffice: the bound (k_bound.hip), the frames it cannot serve
 //    as above, or by the dense kernel when they are too many; all frames by the
