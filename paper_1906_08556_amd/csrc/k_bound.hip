@@ -413,7 +413,7 @@ __device__ inline float bound_limit(const BoundTest& b, float2 cv) {
 // the test with all 32 rows first (19 us at C = 2048; where the bound
 // fails, the sweeps would waste 1.5 ms per 131,072 frames).
 constexpr int kSample = 128;
-constexpr int SP = 4;  // component pairs per workgroup of k_sample_sums
+constexpr int SP = 2;  // component pairs per workgroup of k_sample_sums
 // Costs by that of one dense tile of 128 frames per CU (2.3 ms in FP32 and 1.0 in
 // BF16 at C = 2048, D = 60, proportional to K): the bound's sweeps over F frames b0 +
 // b1 F, dearer by 0.4 of the share that it hands on; further dense rounds of two
@@ -449,7 +449,7 @@ k_sample_sums(const _Float16* __restrict__ xh, const float2* __restrict__ tg, in
     xf[ks] = *reinterpret_cast<const half8*>(xh + g * BK + 16 * ks + 8 * h);
   const half8* W8 = reinterpret_cast<const half8*>(Wf) + (size_t)blockIdx.x * SP * 512 + lane;
   float2* out = sv + (size_t)(32 * wave + l32) * Cpad + (size_t)blockIdx.x * SP * 2 + h;
-#pragma unroll 2
+#pragma unroll
   for (int i = 0; i < SP; ++i) {
     float sq[2] = {0.0f, 0.0f};
 #pragma unroll
@@ -466,28 +466,30 @@ k_sample_sums(const _Float16* __restrict__ xh, const float2* __restrict__ tg, in
   }
 }
 
-// One wave per sampled frame: its best component (on 16 rows, as in sweep 1), that
-// one's exact score, the components that pass.  The last one decides: dec[0] frames for the bound,
-// dec[1] for the dense kernel (all or none); dec[2..4] counters.
-__global__ void __launch_bounds__(64)
+// One workgroup per sampled frame: its best component (on 16 rows, as in sweep 1),
+// that one's exact score, the components that pass.  The last one decides: dec[0]
+// frames for the bound, dec[1] for the dense kernel (all or none); dec[2..4]
+// counters.
+__global__ void __launch_bounds__(256)
 k_sample_count(const float* __restrict__ X, int64_t F, int D, const float2* __restrict__ tg,
                const float2* __restrict__ cb, const int* __restrict__ maxbits, int Cpad,
                float margin, const double* __restrict__ mu, const float* __restrict__ lquad,
                const double* __restrict__ cst, const float2* __restrict__ sv, SampleRule rule,
                int* __restrict__ dec, const int* __restrict__ Fdev) {
-  __shared__ float ds[64];
+  __shared__ float ds[64], wv[4], yp[4][64];
+  __shared__ int wc[4], odd[4], even[4];
   if (Fdev && (int64_t)Fdev[0] < F) F = Fdev[0];
-  const int lane = threadIdx.x, ns = gridDim.x;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, ns = gridDim.x;
   const float S = bound_scale(maxbits), r2 = 0.5f / (S * S);
   bool bad = false;
   int cnt = 0;
-  if (F > 0) {
+  if (F > 0) {  // uniform
     const int64_t g = sample_frame(F, blockIdx.x, ns);
     const float2* v = sv + (size_t)blockIdx.x * Cpad;
     float bv = INFINITY;
     int bc = -1;
-#pragma unroll 4
-    for (int c = lane; c < Cpad; c += 64) {
+#pragma unroll 8
+    for (int c = tid; c < Cpad; c += 256) {
       const float k = v[c].x - cb[c].x * r2;
       bc = k < bv ? c : bc;
       bv = fminf(k, bv);
@@ -499,37 +501,59 @@ k_sample_count(const float* __restrict__ X, int64_t F, int D, const float2* __re
       if (ov < bv || (ov == bv && oc < bc)) bc = oc;
       bv = fminf(bv, ov);
     }
-    bc = __builtin_amdgcn_readfirstlane(bc);
+    if (lane == 0) {
+      wv[w] = bv;
+      wc[w] = bc;
+    }
+    __syncthreads();
+    bv = INFINITY;
+    bc = -1;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (wv[i] < bv || (wv[i] == bv && wc[i] < bc)) {
+        bv = wv[i];
+        bc = wc[i];
+      }
     float M = -INFINITY;
-    if (bc >= 0) {  // uniform; one wave
-      ds[lane] = lane < D ? (float)((double)X[g * D + lane] - mu[(size_t)bc * D + lane]) : 0.0f;
-      __syncthreads();
+    if (bc >= 0) {  // uniform; a quarter of the columns per wave
+      if (tid < 64)
+        ds[lane] = lane < D ? (float)((double)X[g * D + lane] - mu[(size_t)bc * D + lane]) : 0.0f;
       const float4* Lq = reinterpret_cast<const float4*>(lquad) + (size_t)bc * 1024 + lane;
+      float4 l[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) l[q] = Lq[(4 * w + q) * 64];
+      __syncthreads();
       float y = 0.0f;
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const float4 l = Lq[q * 64];
-        y = fmaf(l.x, ds[4 * q], y);
-        y = fmaf(l.y, ds[4 * q + 1], y);
-        y = fmaf(l.z, ds[4 * q + 2], y);
-        y = fmaf(l.w, ds[4 * q + 3], y);
+      for (int q = 0; q < 4; ++q) {
+        const float* d = ds + 16 * w + 4 * q;
+        y = fmaf(l[q].x, d[0], y);
+        y = fmaf(l[q].y, d[1], y);
+        y = fmaf(l[q].z, d[2], y);
+        y = fmaf(l[q].w, d[3], y);
       }
+      yp[w][lane] = y;
+      __syncthreads();
+      y = (yp[0][lane] + yp[1][lane]) + (yp[2][lane] + yp[3][lane]);
       float q = y * y;
 #pragma unroll
       for (int o = 32; o >= 1; o >>= 1) q += __shfl_xor(q, o);
       M = (float)cst[bc] - 0.5f * q;
     }
     const BoundTest b = bound_test(tg[g], S, M, margin, true, cb, bc);
-    // c = lane + 64 i: the parity of the lane is the component's
-#pragma unroll 4
-    for (int c = lane; c < Cpad; c += 64) cnt += v[c].y <= bound_limit(b, cb[c]) ? 1 : 0;
+    // c = tid + 256 i: the parity of the thread is the component's
+#pragma unroll 8
+    for (int c = tid; c < Cpad; c += 256) cnt += v[c].y <= bound_limit(b, cb[c]) ? 1 : 0;
 #pragma unroll
     for (int o = 32; o >= 2; o >>= 1) cnt += __shfl_xor(cnt, o);
-    const int other = __shfl_xor(cnt, 1);
-    bad = !b.good || cnt > SL || other > SL;
-    cnt += other;
+    if (lane == 0) even[w] = cnt;
+    if (lane == 1) odd[w] = cnt;
+    __syncthreads();
+    const int n0 = even[0] + even[1] + even[2] + even[3], n1 = odd[0] + odd[1] + odd[2] + odd[3];
+    bad = !b.good || n0 > SL || n1 > SL;
+    cnt = n0 + n1;
   }
-  if (lane != 0) return;
+  if (tid != 0) return;
   if (bad)
     atomicAdd(dec + 2, 1);
   else
@@ -1323,7 +1347,7 @@ void launch_bound_select(ivx_ctx* ctx, const float* X, int64_t F, int prec, hipS
   if (ns > 0) {
     k_sample_sums<<<ctx->Cpad / (2 * SP), 256, 0, s>>>(xh, tg, F, ctx->Wf, ctx->bmax, ctx->Cpad, ns,
                                                        sv, dec, Fdev);
-    k_sample_count<<<ns, 64, 0, s>>>(X, F, ctx->D, tg, ctx->cb, ctx->bmax, ctx->Cpad,
+    k_sample_count<<<ns, 256, 0, s>>>(X, F, ctx->D, tg, ctx->cb, ctx->bmax, ctx->Cpad,
                                      margin + err - 3.0f, ctx->mu, ctx->lquad, ctx->cst, sv,
                                      rule, dec, Fdev);
     Fdev = dec;
