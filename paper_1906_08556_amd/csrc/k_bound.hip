@@ -35,6 +35,7 @@
 //                   dense kernel's own arithmetic (the same FP32 products and
 //                   fused additions in the same order, or the same BF16 MFMA
 //                   sequence), so that the candidate lists are the dense ones
+//                   (but for the dense kernel's overflows in mid sweep)
 //   k_bound_final   lists sorted into the dense kernel's order, running
 //                   maximum, overflow flag
 //
@@ -575,8 +576,8 @@ k_sample_count(const float* __restrict__ X, int64_t F, int D, const float2* __re
 // of 32 frames per wave (lane l: frame l % 32 of each block, component parity
 // l / 32).  Sweep 1 is bound by the matrix cores (per 32 x 32 block 4 MFMAs, 128
 // cycles, and 21 vector instructions, 84 cycles, which overlap between the four
-// waves of a SIMD) and by power: 4 M frames at C = 2048 take 15.1 ms at 1.64 GHz,
-// 68 % of the cycles in MFMAs.  The FP16 operand of a pair of components (4 KB
+// waves of a SIMD) and by power: 4 M frames at C = 2048 take 15.1 ms at 1.74 GHz,
+// 61 % of the cycles in MFMAs.  The FP16 operand of a pair of components (4 KB
 // per 16 rows) is staged through LDS in fragment order and serves the FB frame
 // blocks of all waves; at one block per wave the LDS reads alone would take as
 // long as the MFMAs.  Sweep 2 reads the sums (16 GB) and forms the second 16
