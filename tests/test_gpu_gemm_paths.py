@@ -2,6 +2,8 @@
 larger than with 64 x 64 tiles and 512 of them fill the device) at ragged edges:
 the E-step's precision product and the selector's products.  Bounds as for these
 steps elsewhere."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -99,6 +101,7 @@ def test_memory_of_a_wide_selector():
         torch.cuda.synchronize()
         return torch.cuda.mem_get_info()[0]
 
+    gc.collect()  # contexts of other tests
     free(0)
     a = free(0)
     assert a - free(B) <= (64 << 20) + 4 * (B * 8 * H + 32 * H) + (8 << 20)
